@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpaf.so")
-SOURCES = ["filter.hip", "whole.hip", "mlp.hip", "api.hip", "stream.hip", "verify.hip", "magnet.hip"]
+SOURCES = ["filter.hip", "flow.hip", "whole.hip", "mlp.hip", "api.hip", "stream.hip", "verify.hip", "magnet.hip"]
 # Measurement aid (VALU issue-rate calibration), a library of its own.
 CALIB_LIB = os.path.join(HERE, "libpaf_calib.so")
 CALIB_SOURCE = "calib.hip"

@@ -560,8 +560,14 @@ paf_status paf_filter(paf_ctx* ctx, const paf_batch* batch, uint32_t filters, co
     sh.waves_per_block = p.wmax > 8 ? 2 : 4;
     sh.lds_bytes = filter_lds_bytes(sh.waves_per_block, p.wmax);
     uint64_t units = p.n_tiles;
-    // SneakySnake alone: the compacting engine, as a full grid of chunks
-    // (a forced layout may set its chunk size and block shape, or turn it off).
+    // SneakySnake alone: the flow engine or the compacting engine, the latter
+    // as a full grid of chunks (a forced layout may set its chunk size and
+    // block shape, or turn it off).
+    if (eng == Engine::Snake && !ctx->layout_forced && flow_serves(p)) {
+        PAF_HIP(hipSetDevice(ctx->device), "hipSetDevice");
+        PAF_HIP(launch_flow(p, emax, ctx->num_cus, (hipStream_t)stream), "filter launch");
+        return PAF_OK;
+    }
     const paf_layout PL = ctx->layout_forced ? ctx->forced : plain_layout(emax);
     if (eng == Engine::Snake && PL.chunk_tiles > 0) {
         eng = compacting_engine(PL, emax, st);

@@ -44,6 +44,8 @@ struct FilterParams {
                                // pairs enter the first window in ascending key order, or NULL
     uint32_t part;             // compacting engine, partitioned maze: sub-maze width in columns
     uint32_t part_cap;         // ... and the most obstacles one sub-maze counts (~0u: no cap)
+    uint32_t waves;            // flow engine: waves of the launch
+    uint32_t probes;           // flow engine: probes per window
 };
 
 // Kernel selection.
@@ -101,6 +103,11 @@ const void* whole_kernel_ptr(bool general, int emax, uint32_t filters);
 size_t filter_lds_bytes(uint32_t waves_per_block, uint32_t wmax);
 // LDS of a compacting launch (keyed launches sort inside the list itself).
 size_t chunk_lds_bytes(uint32_t waves_per_block, bool general, int emax, uint32_t chunk_tiles, uint32_t lpp);
+
+// flow.hip: SneakySnake with every lane at a column of its own; flow_serves:
+// the batches paf_filter runs there.
+bool flow_serves(const FilterParams& p);
+hipError_t launch_flow(FilterParams p, int emax, int num_cus, hipStream_t stream);
 
 // verify.hip: banded edit distance of the selected pairs (sel: accept-bit
 // words, or NULL for every pair).
