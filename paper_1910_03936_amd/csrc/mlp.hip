@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 #include <vector>
 
 #include "paf_internal.h"
@@ -71,24 +72,30 @@ __host__ __device__ __forceinline__ int l2_hidden(int kt, int g, int j) {
 // ---------------------------------------------------------------------------
 // Working copies of the weights: bf16 row-major W1 [h][f], W2 [o][h] and its
 // transpose, W3 rounded to bf16 values, and matrix-core fragment orders.
+__device__ __forceinline__ void store_working_copies(uint32_t i, float w, uint16_t* w1b, uint16_t* w2b, uint16_t* w2tb,
+                                                     float* w3r, uint16_t* w1f, uint16_t* w2f) {
+    const uint16_t v = bf16_bits(w);
+    if (i < (uint32_t)OFF_B1) {
+        const uint32_t h = i / kFeat, f = i % kFeat;
+        w1b[i] = v;
+        // Fragment order: m-tile h / 16, k-tile f / 32, lane, element.
+        w1f[(((h >> 4) * 2 + (f >> 5)) * 64 + ((f >> 3) & 3u) * 16 + (h & 15u)) * 8 + (f & 7u)] = v;
+    } else if (i >= (uint32_t)OFF_W2 && i < (uint32_t)OFF_B2) {
+        const uint32_t x = i - OFF_W2, o = x / kHid, h = x % kHid;
+        w2b[x] = v;
+        w2tb[h * kHid + o] = v;
+        // The element and lane group that l2_hidden gives hidden unit h.
+        const uint32_t kt = h >> 5, r = h & 31u, g = (r & 15u) >> 2, j = (r & 3u) + (r >= 16u ? 4u : 0u);
+        w2f[(((o >> 4) * 4 + kt) * 64 + g * 16 + (o & 15u)) * 8 + j] = v;
+    } else if (i >= (uint32_t)OFF_W3 && i < (uint32_t)OFF_B3) {
+        w3r[i - OFF_W3] = bf16_round(w);
+    }
+}
+
 __global__ void round_kernel(const float* master, uint16_t* w1b, uint16_t* w2b, uint16_t* w2tb,
                              float* w3r, uint16_t* w1f, uint16_t* w2f) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < kHid * kFeat) {
-        w1b[i] = bf16_bits(master[OFF_W1 + i]);
-        const int j = i % 8, lane = (i / 8) % 64, kt = (i / 512) % 2, mt = i / 1024;
-        const int h = 16 * mt + lane % 16, f = 32 * kt + 8 * (lane / 16) + j;
-        w1f[i] = bf16_bits(master[OFF_W1 + h * kFeat + f]);
-    }
-    if (i < kHid * kHid) {
-        const uint16_t v = bf16_bits(master[OFF_W2 + i]);
-        w2b[i] = v;
-        w2tb[(i % kHid) * kHid + i / kHid] = v;
-        const int j = i % 8, lane = (i / 8) % 64, kt = (i / 512) % 4, mt = i / 2048;
-        const int o = 16 * mt + lane % 16, h = l2_hidden(kt, lane / 16, j);
-        w2f[i] = bf16_bits(master[OFF_W2 + o * kHid + h]);
-    }
-    if (i < kHid) w3r[i] = bf16_round(master[OFF_W3 + i]);
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < (uint32_t)PAF_MLP_NPARAMS) store_working_copies(i, master[i], w1b, w2b, w2tb, w3r, w1f, w2f);
 }
 
 // ---------------------------------------------------------------------------
@@ -851,158 +858,307 @@ __global__ void __launch_bounds__(256) bucket_scatter_kernel(const uint8_t* buck
 }
 
 // ---------------------------------------------------------------------------
-// Training.  TN GEMM on the matrix cores: C[m][n] = sum_k A[m][k] B[n][k]
-// (both operands k-contiguous bf16), fp32 accumulation; M, N multiples of
-// 64, K and the k-chunk multiples of 32.  Block = 4 waves, 64 x 64 tile.
-enum GemmMode { G_PARTIAL = 0, G_BIAS_RELU = 1, G_MASK = 2 };
-struct Gemm {
-    const uint16_t* A;
-    int lda;
-    const uint16_t* B;
-    int ldb;
-    int M, N, K, kchunk;
-    int mode;
-    const float* bias;
-    float* outf;
-    int ldo;
-    uint16_t* outb;
-    int ldob;
-    uint16_t* outbT;
-    int ldobT;
-    const uint16_t* mask;
-    int ldmask;
+// Training.  One kernel takes 64-row tiles of a minibatch through the forward
+// pass, the loss and the backward pass with every activation in LDS; its block
+// keeps the weight gradients of its tiles in matrix-core accumulators and
+// writes them once, as one of `splits` partial sums, and a second kernel adds
+// the partials up in order and applies Adam.  A kernel per layer and reduction
+// had taken 19 launches with every activation through HBM and a head of one
+// thread per row on 16 blocks: 4096 rows 193 -> 21 us, of which this kernel 14.4
+// and the update 4.3.  One wave per SIMD (four waves a block) measured 16.6: the
+// tile's phases wait for LDS and barriers, not for the matrix cores.
+// Matrix products take their terms in the order of the layer-by-layer form
+// (k-steps of 32 from zero, the bias added after), so activations are the
+// same bit for bit.
+//
+// Matrix products are C[m][n] = sum_k A[m][k] B[n][k], both operands
+// k-contiguous bf16, fp32 accumulation; lane (q16, grp) gets rows 4 grp + i,
+// column q16 of a 16 x 16 tile.
+constexpr int kTile = 64;            // rows per tile
+constexpr int kRowPad = 8;           // bf16 words between LDS rows, against bank conflicts
+constexpr uint32_t kMaxSplit = 256;  // partial sums of the weight gradients
+constexpr uint32_t kPartWords = 25088;   // words per partial: PAF_MLP_NPARAMS, then the loss
+
+struct TrainLds {
+    uint16_t X[kTile][kFeat + kRowPad];       // inputs
+    uint16_t XT[kFeat][kTile + kRowPad];
+    uint16_t H1[kTile][kHid + kRowPad];       // layer 1
+    uint16_t H1T[kHid][kTile + kRowPad];
+    float H2[kTile][kHid + 1];                // layer 2
+    uint16_t D2[kTile][kHid + kRowPad];       // gradient at layer 2
+    uint16_t D2T[kHid][kTile + kRowPad];
+    uint16_t D1T[kHid][kTile + kRowPad];      // gradient at layer 1
+    float dy[kTile], w3[kHid];
+    float colsum[2][4][kHid];                 // [b2, w3][quarter of the rows]
+};
+struct ForwardLds {
+    uint16_t X[kTile][kFeat + kRowPad];
+    uint16_t H1[kTile][kHid + kRowPad];
+    float H2[kTile][kHid + 1];
+    float w3[kHid];
 };
 
-__global__ void __launch_bounds__(256) gemm_tn_kernel(Gemm g) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+struct TrainArgs {
+    const float* feat;     // [n][64]
+    const float* tgt;      // [n] (training)
+    uint32_t n;
+    uint32_t split_rows;   // rows per block, a multiple of kTile
+    const uint16_t* w1b;
+    const uint16_t* w2b;
+    const uint16_t* w2tb;
+    const float* w3r;
+    const float* master;
+    float* pred;           // [n] (inference)
+    float* part;           // [splits][kPartWords] (training)
+};
+
+__device__ __forceinline__ bf16x8 frag(const uint16_t* row, int k) { return *reinterpret_cast<const bf16x8*>(row + k); }
+
+constexpr int kMlpThreads = 512;   // eight waves: one 16-wide strip of hidden units each
+
+template <bool TRAIN>
+__global__ void __launch_bounds__(kMlpThreads) mlp_kernel(TrainArgs a) {
+    __shared__ __attribute__((aligned(16))) typename std::conditional<TRAIN, TrainLds, ForwardLds>::type L;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int q16 = lane & 15, grp = lane >> 4;
-    const int m0 = blockIdx.x * 64 + (wave >> 1) * 32;
-    const int n0 = blockIdx.y * 64 + (wave & 1) * 32;
-    const int kb = blockIdx.z * g.kchunk;
-    const int ke = min(g.K, kb + g.kchunk);
-    f32x4 acc[2][2];
+    const uint64_t row0 = (uint64_t)blockIdx.x * a.split_rows;
+    const uint32_t rows = (uint32_t)min<uint64_t>(a.split_rows, a.n - row0);
+    const float b3 = a.master[OFF_B3];
+    // The wave's weights (of hidden unit `unit`), loaded together while the
+    // first tile's inputs come in.
+    const int unit = 16 * wave + q16;
+    bf16x8 w1[2], w2[4], w2t[TRAIN ? 4 : 1];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int k = 0; k < 2; ++k) w1[k] = frag(a.w1b + unit * kFeat, 32 * k + 8 * grp);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k = kb; k < ke; k += 32) {
-        bf16x8 a[2], b[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-            a[i] = *reinterpret_cast<const bf16x8*>(g.A + (size_t)(m0 + 16 * i + q16) * g.lda + k + 8 * grp);
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            b[j] = *reinterpret_cast<const bf16x8*>(g.B + (size_t)(n0 + 16 * j + q16) * g.ldb + k + 8 * grp);
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = mfma(a[i], b[j], acc[i][j]);
+    for (int k = 0; k < 4; ++k) {
+        w2[k] = frag(a.w2b + unit * kHid, 32 * k + 8 * grp);
+        if constexpr (TRAIN) w2t[k] = frag(a.w2tb + unit * kHid, 32 * k + 8 * grp);
     }
+    const float bias1 = a.master[OFF_B1 + unit], bias2 = a.master[OFF_B2 + unit];
+    if (tid < kHid) L.w3[tid] = a.w3r[tid];
+    // The block's weight gradients: rows 16 wave .. + 15 of dW2 and dW1.
+    f32x4 gw2[TRAIN ? 8 : 1], gw1[TRAIN ? 4 : 1];
+    float gb1 = 0.0f, gb2 = 0.0f, gw3 = 0.0f, gb3 = 0.0f, loss = 0.0f;
+    if constexpr (TRAIN) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < 8; ++j) gw2[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 4; ++j) gw1[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    for (uint32_t t0 = 0; t0 < rows; t0 += kTile) {
+        // Inputs (rows past the batch are zero): a lane per row, eight of its
+        // features per wave.
+        {
+            const int c = 8 * wave;
+            uint16_t v[8];
+            const bool real = t0 + lane < rows;
+            const float* src = a.feat + (row0 + t0 + (real ? lane : 0)) * kFeat + c;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = m0 + 16 * i + 4 * grp + e;
-                const int col = n0 + 16 * j + q16;
-                float v = acc[i][j][e];
-                if (g.mode == G_PARTIAL) {
-                    g.outf[(size_t)blockIdx.z * g.M * g.N + (size_t)row * g.N + col] = v;
-                    continue;
-                }
-                if (g.mode == G_BIAS_RELU) {
-                    v = fmaxf(v + g.bias[col], 0.0f);
-                } else {  // G_MASK: gradient through the ReLU of the stored activation
-                    const uint16_t h = g.mask[(size_t)row * g.ldmask + col];
-                    v = ((h & 0x7fffu) != 0u && !(h & 0x8000u)) ? v : 0.0f;
-                }
-                if (g.outf) g.outf[(size_t)row * g.ldo + col] = v;
-                const uint16_t vb = bf16_bits(v);
-                if (g.outb) g.outb[(size_t)row * g.ldob + col] = vb;
-                if (g.outbT) g.outbT[(size_t)col * g.ldobT + row] = vb;
+            for (int j = 0; j < 8; ++j) v[j] = real ? bf16_bits(src[j]) : (uint16_t)0;
+            *reinterpret_cast<uint4*>(&L.X[lane][c]) =
+                make_uint4(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16, v[4] | (uint32_t)v[5] << 16,
+                           v[6] | (uint32_t)v[7] << 16);
+            if constexpr (TRAIN) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) L.XT[c + j][lane] = v[j];
             }
-}
-
-// Features (fp32, n rows) -> bf16 [Np][64] and its transpose [64][Np]; rows
-// past n are zero.
-__global__ void to_bf16_kernel(const float* f, uint32_t n, uint32_t Np, uint16_t* X, uint16_t* XT) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= Np * kFeat) return;
-    const uint32_t p = i / kFeat, c = i % kFeat;
-    const uint16_t v = p < n ? bf16_bits(f[(size_t)p * kFeat + c]) : (uint16_t)0;
-    X[i] = v;
-    XT[(size_t)c * Np + p] = v;
-}
-
-// Head, loss and its gradient: y = w3 . h2 + b3 per row; for rows < n,
-// dy = 2 (y - t) / n and dL/dh2 = dy w3 where h2 > 0.
-// Rows p < n are real; predictions are written for them only.  Without
-// targets (inference) the gradients are zero.
-__global__ void head_kernel(const float* H2, const float* w3r, const float* master, const float* tgt,
-                            uint32_t n, uint32_t Np, float* pred, float* sq, float* dy, uint16_t* dH2b,
-                            uint16_t* dH2T, float* dH2f) {
-    const uint32_t p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= Np) return;
-    const float* h = H2 + (size_t)p * kHid;
-    float y = 0.0f;
-    for (int o = 0; o < kHid; ++o) y += w3r[o] * h[o];
-    y += master[OFF_B3];
-    float d = 0.0f;
-    if (p < n && tgt) {
-        const float e = y - tgt[p];
-        sq[p] = e * e;
-        d = 2.0f * e / (float)n;
-    } else {
-        sq[p] = 0.0f;
-    }
-    if (p < n) pred[p] = y;
-    dy[p] = d;
-    for (int o = 0; o < kHid; ++o) {
-        const float g = h[o] > 0.0f ? d * w3r[o] : 0.0f;
-        dH2f[(size_t)p * kHid + o] = g;
-        const uint16_t gb = bf16_bits(g);
-        dH2b[(size_t)p * kHid + o] = gb;
-        dH2T[(size_t)o * Np + p] = gb;
-    }
-}
-
-// out[j] = scale * sum_p w[p] X[p][j] (w = 1 when NULL); fixed reduction order.
-__global__ void __launch_bounds__(256) reduce_rows_kernel(const float* X, uint32_t rows, uint32_t cols,
-                                                          const float* w, float scale, float* out) {
-    __shared__ float red[256];
-    const uint32_t j = blockIdx.x;
-    float s = 0.0f;
-    for (uint32_t p = threadIdx.x; p < rows; p += blockDim.x) s += (w ? w[p] : 1.0f) * X[(size_t)p * cols + j];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (uint32_t o = blockDim.x / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+        }
+        float target = 0.0f;
+        if constexpr (TRAIN)
+            if (wave == 0 && t0 + lane < rows) target = a.tgt[row0 + t0 + lane];
+        __syncthreads();
+        {
+            f32x4 acc[4] = {};
+#pragma unroll
+            for (int k = 0; k < kFeat; k += 32)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i] = mfma(frag(L.X[16 * i + q16], k + 8 * grp), w1[k / 32], acc[i]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint16_t v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[e] = bf16_bits(fmaxf(acc[i][e] + bias1, 0.0f));
+                    L.H1[16 * i + 4 * grp + e][unit] = v[e];
+                }
+                if constexpr (TRAIN)
+                    *reinterpret_cast<uint2*>(&L.H1T[unit][16 * i + 4 * grp]) =
+                        make_uint2(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16);
+            }
+        }
+        __syncthreads();
+        {
+            f32x4 acc[4] = {};
+#pragma unroll
+            for (int k = 0; k < kHid; k += 32)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i] = mfma(frag(L.H1[16 * i + q16], k + 8 * grp), w2[k / 32], acc[i]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) L.H2[16 * i + 4 * grp + e][unit] = fmaxf(acc[i][e] + bias2, 0.0f);
+        }
+        __syncthreads();
+        // Head (a lane per row), loss and its gradient.
+        if (wave == 0) {
+            float y = 0.0f;
+#pragma unroll 16
+            for (int o = 0; o < kHid; ++o) y += L.w3[o] * L.H2[lane][o];
+            y += b3;
+            const bool real = t0 + lane < rows;
+            if constexpr (TRAIN) {
+                float d = 0.0f, q = 0.0f;
+                if (real) {
+                    const float e = y - target;
+                    q = e * e;
+                    d = 2.0f * e / (float)a.n;
+                }
+                L.dy[lane] = d;
+                gb3 += d;
+                loss += q;
+            } else if (real) {
+                a.pred[row0 + t0 + lane] = y;
+            }
+        }
+        if constexpr (TRAIN) {
+            __syncthreads();
+            // Gradient at layer 2: a thread per hidden unit and quarter of the rows.
+            {
+                const int o = tid & 127, p0 = (tid >> 7) * 16;
+                const float w = L.w3[o];
+#pragma unroll
+                for (int p = p0; p < p0 + 16; p += 8) {
+                    uint16_t v[8];
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        const float h = L.H2[p + r][o], d = L.dy[p + r];
+                        const float g = h > 0.0f ? d * w : 0.0f;
+                        gb2 += g;
+                        gw3 += d * h;
+                        v[r] = bf16_bits(g);
+                        L.D2[p + r][o] = v[r];
+                    }
+                    *reinterpret_cast<uint4*>(&L.D2T[o][p]) =
+                        make_uint4(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16, v[4] | (uint32_t)v[5] << 16,
+                                   v[6] | (uint32_t)v[7] << 16);
+                }
+            }
+            __syncthreads();
+            // Gradient at layer 1, through the ReLU of the stored activation.
+            {
+                f32x4 acc[4] = {};
+#pragma unroll
+                for (int k = 0; k < kHid; k += 32)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[i] = mfma(frag(L.D2[16 * i + q16], k + 8 * grp), w2t[k / 32], acc[i]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    uint16_t v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint16_t act = L.H1T[unit][16 * i + 4 * grp + e];   // never negative
+                        const float g = (act & 0x7fffu) != 0u && !(act & 0x8000u) ? acc[i][e] : 0.0f;
+                        gb1 += g;
+                        v[e] = bf16_bits(g);
+                    }
+                    *reinterpret_cast<uint2*>(&L.D1T[unit][16 * i + 4 * grp]) =
+                        make_uint2(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16);
+                }
+            }
+            __syncthreads();
+            // Weight gradients over the tile's rows.
+#pragma unroll
+            for (int k = 0; k < kTile; k += 32) {
+                const bf16x8 d2 = frag(L.D2T[unit], k + 8 * grp), d1 = frag(L.D1T[unit], k + 8 * grp);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) gw2[j] = mfma(d2, frag(L.H1T[16 * j + q16], k + 8 * grp), gw2[j]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) gw1[j] = mfma(d1, frag(L.XT[16 * j + q16], k + 8 * grp), gw1[j]);
+            }
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[j] = red[0] * scale;
+    if constexpr (TRAIN) {
+        float* part = a.part + (size_t)blockIdx.x * kPartWords;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int r = 16 * wave + 4 * grp + e;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) part[OFF_W2 + r * kHid + 16 * j + q16] = gw2[j][e];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[OFF_W1 + r * kFeat + 16 * j + q16] = gw1[j][e];
+        }
+        gb1 += __shfl_xor(gb1, 16);
+        gb1 += __shfl_xor(gb1, 32);
+        if (grp == 0) part[OFF_B1 + unit] = gb1;
+        L.colsum[0][tid >> 7][tid & 127] = gb2;
+        L.colsum[1][tid >> 7][tid & 127] = gw3;
+        if (wave == 0) {
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                gb3 += __shfl_xor(gb3, o);
+                loss += __shfl_xor(loss, o);
+            }
+            if (lane == 0) {
+                part[OFF_B3] = gb3;
+                part[PAF_MLP_NPARAMS] = loss;
+            }
+        }
+        __syncthreads();
+        if (tid < 2 * kHid) {
+            const float* c = L.colsum[tid >> 7][0] + (tid & 127);
+            part[(tid >> 7 ? OFF_W3 : OFF_B2) + (tid & 127)] = c[0] + c[kHid] + c[2 * kHid] + c[3 * kHid];
+        }
+    }
 }
 
-__global__ void splitk_reduce_kernel(const float* part, uint32_t S, uint32_t MN, float* out) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= MN) return;
-    float s = 0.0f;
-    for (uint32_t k = 0; k < S; ++k) s += part[(size_t)k * MN + i];
-    out[i] = s;
-}
+// Adds the partial gradients up in order (loads of 16 partials in flight),
+// then Adam (Kingma and Ba, 2015) on the fp32 master weights and the bf16
+// working copies of the new weights (unless lr is 0).
+struct UpdateArgs {
+    const float* part;
+    uint32_t splits;
+    float* grad;
+    float* grad_out;   // optional copy of the gradients
+    float* loss_out;   // optional mean loss
+    float inv_n;
+    float *master, *adam_m, *adam_v;
+    float lr, c1, c2;
+    uint16_t *w1b, *w2b, *w2tb, *w1f, *w2f;
+    float* w3r;
+};
 
-// Adam (Kingma and Ba, 2015) on the fp32 master weights.
-__global__ void adam_kernel(float* w, const float* g, float* m, float* v, uint32_t n, float lr, float b1,
-                            float b2, float eps, float c1, float c2) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float mh = mi / c1, vh = vi / c2;
-    w[i] -= lr * mh / (sqrtf(vh) + eps);
+__global__ void __launch_bounds__(64) mlp_update_kernel(UpdateArgs a) {
+    const uint32_t i = blockIdx.x * 64u + threadIdx.x;
+    if (i > (uint32_t)PAF_MLP_NPARAMS) return;
+    float g = 0.0f;
+    const float* src = a.part + i;
+    uint32_t k = 0;
+    for (; k + 16 <= a.splits; k += 16) {
+        float v[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) v[j] = src[(size_t)(k + j) * kPartWords];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) g += v[j];
+    }
+    for (; k < a.splits; ++k) g += src[(size_t)k * kPartWords];
+    if (i == (uint32_t)PAF_MLP_NPARAMS) {
+        if (a.loss_out) *a.loss_out = g * a.inv_n;
+        return;
+    }
+    a.grad[i] = g;
+    if (a.grad_out) a.grad_out[i] = g;
+    if (!(a.lr > 0.0f)) return;
+    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+    const float mi = b1 * a.adam_m[i] + (1.0f - b1) * g;
+    const float vi = b2 * a.adam_v[i] + (1.0f - b2) * g * g;
+    a.adam_m[i] = mi;
+    a.adam_v[i] = vi;
+    const float mh = mi / a.c1, vh = vi / a.c2;
+    const float w = a.master[i] - a.lr * mh / (sqrtf(vh) + eps);
+    a.master[i] = w;
+    store_working_copies(i, w, a.w1b, a.w2b, a.w2tb, a.w3r, a.w1f, a.w2f);
 }
 
 __global__ void u16_to_f32_kernel(const uint16_t* a, uint64_t n, float* out) {
@@ -1033,51 +1189,6 @@ const void* feature_kernel_for(int ef, bool fused, bool two_sets = false) {
 #undef PAF_FCASE
         default: return nullptr;
     }
-}
-
-// ---------------------------------------------------------------------------
-// Training workspace carved from one allocation.
-struct TrainWs {
-    uint16_t *X, *XT, *H1b, *H1T, *dH2b, *dH2T, *dH1T;
-    float *H2f, *pred, *sq, *dy, *dH2f, *dH1f, *part, *tgt;
-};
-constexpr uint32_t kMaxSplit = 64;
-
-size_t train_ws_bytes(size_t Np) {
-    return Np * kFeat * 2 * 2 + Np * kHid * 2 * 5 + Np * kHid * 4 * 3 + Np * 4 * 4 +
-           (size_t)kMaxSplit * kHid * kHid * 4 + 4096;
-}
-
-TrainWs carve(void* base, size_t Np) {
-    char* p = static_cast<char*>(base);
-    auto take = [&](size_t bytes) {
-        char* r = p;
-        p += (bytes + 255) & ~size_t(255);
-        return r;
-    };
-    TrainWs w;
-    w.X = (uint16_t*)take(Np * kFeat * 2);
-    w.XT = (uint16_t*)take(Np * kFeat * 2);
-    w.H1b = (uint16_t*)take(Np * kHid * 2);
-    w.H1T = (uint16_t*)take(Np * kHid * 2);
-    w.dH2b = (uint16_t*)take(Np * kHid * 2);
-    w.dH2T = (uint16_t*)take(Np * kHid * 2);
-    w.dH1T = (uint16_t*)take(Np * kHid * 2);
-    w.H2f = (float*)take(Np * kHid * 4);
-    w.dH2f = (float*)take(Np * kHid * 4);
-    w.dH1f = (float*)take(Np * kHid * 4);
-    w.pred = (float*)take(Np * 4);
-    w.sq = (float*)take(Np * 4);
-    w.dy = (float*)take(Np * 4);
-    w.tgt = (float*)take(Np * 4);
-    w.part = (float*)take((size_t)kMaxSplit * kHid * kHid * 4);
-    return w;
-}
-
-hipError_t gemm(const Gemm& g, hipStream_t s) {
-    const int splits = g.mode == G_PARTIAL ? (g.K + g.kchunk - 1) / g.kchunk : 1;
-    hipLaunchKernelGGL(gemm_tn_kernel, dim3(g.M / 64, g.N / 64, splits), dim3(256), 0, s, g);
-    return hipGetLastError();
 }
 
 }  // namespace
@@ -1152,7 +1263,7 @@ hipError_t launch_bucket_sort(const uint8_t* bucket, uint64_t n, uint32_t* count
 }
 
 hipError_t mlp_round_weights(MlpDev& m, hipStream_t s) {
-    hipLaunchKernelGGL(round_kernel, dim3(kHid * kHid / 256), dim3(256), 0, s, m.master, m.w1b, m.w2b, m.w2tb,
+    hipLaunchKernelGGL(round_kernel, dim3((PAF_MLP_NPARAMS + 255) / 256), dim3(256), 0, s, m.master, m.w1b, m.w2b, m.w2tb,
                        m.w3r, m.w1f, m.w2f);
     return hipGetLastError();
 }
@@ -1169,75 +1280,57 @@ paf_status need_model(paf_ctx* ctx) {
     return PAF_OK;
 }
 
-paf_status ensure_train_ws(paf_ctx* ctx, size_t Np) {
+paf_status ensure_train_ws(paf_ctx* ctx, size_t splits) {
     MlpDev& m = ctx->mlp;
-    if (m.ws_rows >= Np) return PAF_OK;
+    if (m.ws_splits >= splits) return PAF_OK;
     if (m.ws) hipFree(m.ws);
     m.ws = nullptr;
-    m.ws_rows = 0;
-    if (hipMalloc(&m.ws, train_ws_bytes(Np)) != hipSuccess) return fail(PAF_ERR_NOMEM, "training workspace");
-    m.ws_rows = Np;
+    m.ws_splits = 0;
+    if (hipMalloc(&m.ws, splits * kPartWords * sizeof(float)) != hipSuccess)
+        return fail(PAF_ERR_NOMEM, "training workspace");
+    m.ws_splits = splits;
     return PAF_OK;
+}
+
+// Rows per block of a training step: one tile, until the minibatch has more
+// than kMaxSplit tiles (a partial sum is 100 KB, written and read once).
+uint32_t rows_per_split(uint32_t n) {
+    const uint32_t tiles = (n + kTile - 1) / kTile;
+    return (tiles + kMaxSplit - 1) / kMaxSplit * kTile;
 }
 
 // Forward, loss and gradients of one minibatch; Adam step when lr > 0.
 paf_status train_step(paf_ctx* ctx, const float* feat, const float* tgt, uint32_t n, float lr, hipStream_t s,
-                      float* loss_out) {
+                      float* loss_out, float* grad_out) {
     MlpDev& m = ctx->mlp;
-    const uint32_t Np = (n + 63u) & ~63u;
-    paf_status st = ensure_train_ws(ctx, Np);
+    const uint32_t per = rows_per_split(n), splits = (n + per - 1) / per;
+    paf_status st = ensure_train_ws(ctx, splits);
     if (st != PAF_OK) return st;
-    TrainWs w = carve(m.ws, Np);
-    hipLaunchKernelGGL(to_bf16_kernel, dim3((Np * kFeat + 255) / 256), dim3(256), 0, s, feat, n, Np, w.X, w.XT);
-    Gemm g{};
-    // Layer 1: H1 = relu(X W1^T + b1)
-    g = Gemm{w.X, kFeat, m.w1b, kFeat, (int)Np, kHid, kFeat, kFeat, G_BIAS_RELU, m.master + OFF_B1,
-             nullptr, 0, w.H1b, kHid, w.H1T, (int)Np, nullptr, 0};
-    PAF_HIP(gemm(g, s), "layer 1");
-    // Layer 2: H2 = relu(H1 W2^T + b2)
-    g = Gemm{w.H1b, kHid, m.w2b, kHid, (int)Np, kHid, kHid, kHid, G_BIAS_RELU, m.master + OFF_B2,
-             w.H2f, kHid, nullptr, 0, nullptr, 0, nullptr, 0};
-    PAF_HIP(gemm(g, s), "layer 2");
-    hipLaunchKernelGGL(head_kernel, dim3((Np + 255) / 256), dim3(256), 0, s, w.H2f, m.w3r, m.master, tgt, n, Np,
-                       w.pred, w.sq, w.dy, w.dH2b, w.dH2T, w.dH2f);
-    float* G = m.grad;
-    hipLaunchKernelGGL(reduce_rows_kernel, dim3(kHid), dim3(256), 0, s, w.H2f, Np, (uint32_t)kHid, w.dy, 1.0f,
-                       G + OFF_W3);
-    hipLaunchKernelGGL(reduce_rows_kernel, dim3(1), dim3(256), 0, s, w.dy, Np, 1u, (const float*)nullptr, 1.0f,
-                       G + OFF_B3);
-    hipLaunchKernelGGL(reduce_rows_kernel, dim3(kHid), dim3(256), 0, s, w.dH2f, Np, (uint32_t)kHid,
-                       (const float*)nullptr, 1.0f, G + OFF_B2);
-    if (loss_out)
-        hipLaunchKernelGGL(reduce_rows_kernel, dim3(1), dim3(256), 0, s, w.sq, Np, 1u, (const float*)nullptr,
-                           1.0f / (float)n, loss_out);
-    // dW2 = dH2^T H1 (split over the batch)
-    const int kc = (int)std::max<uint32_t>(64u, ((Np + kMaxSplit - 1) / kMaxSplit + 31u) & ~31u);
-    const uint32_t S = (Np + kc - 1) / kc;
-    g = Gemm{w.dH2T, (int)Np, w.H1T, (int)Np, kHid, kHid, (int)Np, kc, G_PARTIAL, nullptr,
-             w.part, kHid, nullptr, 0, nullptr, 0, nullptr, 0};
-    PAF_HIP(gemm(g, s), "dW2");
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(kHid * kHid / 256), dim3(256), 0, s, w.part, S,
-                       (uint32_t)(kHid * kHid), G + OFF_W2);
-    // dH1 = (dH2 W2) * relu'(H1)
-    g = Gemm{w.dH2b, kHid, m.w2tb, kHid, (int)Np, kHid, kHid, kHid, G_MASK, nullptr,
-             w.dH1f, kHid, nullptr, 0, w.dH1T, (int)Np, w.H1b, kHid};
-    PAF_HIP(gemm(g, s), "dH1");
-    hipLaunchKernelGGL(reduce_rows_kernel, dim3(kHid), dim3(256), 0, s, w.dH1f, Np, (uint32_t)kHid,
-                       (const float*)nullptr, 1.0f, G + OFF_B1);
-    // dW1 = dH1^T X
-    g = Gemm{w.dH1T, (int)Np, w.XT, (int)Np, kHid, kFeat, (int)Np, kc, G_PARTIAL, nullptr,
-             w.part, kFeat, nullptr, 0, nullptr, 0, nullptr, 0};
-    PAF_HIP(gemm(g, s), "dW1");
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(kHid * kFeat / 256), dim3(256), 0, s, w.part, S,
-                       (uint32_t)(kHid * kFeat), G + OFF_W1);
+    const TrainArgs t{feat, tgt, n, per, m.w1b, m.w2b, m.w2tb, m.w3r, m.master, nullptr, (float*)m.ws};
+    hipLaunchKernelGGL(mlp_kernel<true>, dim3(splits), dim3(kMlpThreads), 0, s, t);
+    UpdateArgs u{};
+    u.part = (const float*)m.ws;
+    u.splits = splits;
+    u.grad = m.grad;
+    u.grad_out = grad_out;
+    u.loss_out = loss_out;
+    u.inv_n = 1.0f / (float)n;
+    u.master = m.master;
+    u.adam_m = m.adam_m;
+    u.adam_v = m.adam_v;
+    u.lr = lr;
     if (lr > 0.0f) {
         m.step += 1;
-        const float b1 = 0.9f, b2 = 0.999f;
-        const float c1 = 1.0f - powf(b1, (float)m.step), c2 = 1.0f - powf(b2, (float)m.step);
-        hipLaunchKernelGGL(adam_kernel, dim3((PAF_MLP_NPARAMS + 255) / 256), dim3(256), 0, s, m.master, G,
-                           m.adam_m, m.adam_v, (uint32_t)PAF_MLP_NPARAMS, lr, b1, b2, 1e-8f, c1, c2);
-        PAF_HIP(mlp_round_weights(m, s), "weight rounding");
+        u.c1 = 1.0f - powf(0.9f, (float)m.step);
+        u.c2 = 1.0f - powf(0.999f, (float)m.step);
     }
+    u.w1b = m.w1b;
+    u.w2b = m.w2b;
+    u.w2tb = m.w2tb;
+    u.w1f = m.w1f;
+    u.w2f = m.w2f;
+    u.w3r = m.w3r;
+    hipLaunchKernelGGL(mlp_update_kernel, dim3(PAF_MLP_NPARAMS / 64 + 1), dim3(64), 0, s, u);
     PAF_HIP(hipGetLastError(), "training step");
     return PAF_OK;
 }
@@ -1344,23 +1437,12 @@ paf_status paf_mlp_forward(paf_ctx* ctx, const float* features, uint64_t n, floa
     ScratchScope scope(ctx, (hipStream_t)stream);
     if (scope.st != PAF_OK) return scope.st;
     hipStream_t s = (hipStream_t)stream;
-    MlpDev& m = ctx->mlp;
-    const uint64_t chunk = 65536;
+    const MlpDev& m = ctx->mlp;
+    const uint64_t chunk = 1u << 30;
     for (uint64_t a = 0; a < n; a += chunk) {
         const uint32_t k = (uint32_t)std::min<uint64_t>(chunk, n - a);
-        const uint32_t Np = (k + 63u) & ~63u;
-        if ((st = ensure_train_ws(ctx, Np)) != PAF_OK) return st;
-        TrainWs w = carve(m.ws, Np);
-        hipLaunchKernelGGL(to_bf16_kernel, dim3((Np * kFeat + 255) / 256), dim3(256), 0, s, features + a * kFeat,
-                           k, Np, w.X, w.XT);
-        Gemm g = Gemm{w.X, kFeat, m.w1b, kFeat, (int)Np, kHid, kFeat, kFeat, G_BIAS_RELU, m.master + OFF_B1,
-                      nullptr, 0, w.H1b, kHid, nullptr, 0, nullptr, 0};
-        PAF_HIP(gemm(g, s), "layer 1");
-        g = Gemm{w.H1b, kHid, m.w2b, kHid, (int)Np, kHid, kHid, kHid, G_BIAS_RELU, m.master + OFF_B2,
-                 w.H2f, kHid, nullptr, 0, nullptr, 0, nullptr, 0};
-        PAF_HIP(gemm(g, s), "layer 2");
-        hipLaunchKernelGGL(head_kernel, dim3((Np + 255) / 256), dim3(256), 0, s, w.H2f, m.w3r, m.master,
-                           (const float*)nullptr, k, Np, out + a, w.sq, w.dy, w.dH2b, w.dH2T, w.dH2f);
+        const TrainArgs t{features + a * kFeat, nullptr, k, kTile, m.w1b, m.w2b, m.w2tb, m.w3r, m.master, out + a, nullptr};
+        hipLaunchKernelGGL(mlp_kernel<false>, dim3((k + kTile - 1) / kTile), dim3(kMlpThreads), 0, s, t);
         PAF_HIP(hipGetLastError(), "forward");
     }
     return PAF_OK;
@@ -1377,10 +1459,7 @@ paf_status paf_mlp_train_step(paf_ctx* ctx, const float* features, const float* 
     ScratchScope scope(ctx, (hipStream_t)stream);
     if (scope.st != PAF_OK) return scope.st;
     hipStream_t s = (hipStream_t)stream;
-    if ((st = train_step(ctx, features, targets, (uint32_t)n, lr, s, loss)) != PAF_OK) return st;
-    if (grads)
-        PAF_HIP(hipMemcpyAsync(grads, ctx->mlp.grad, PAF_MLP_NPARAMS * 4, hipMemcpyDeviceToDevice, s), "grads");
-    return PAF_OK;
+    return train_step(ctx, features, targets, (uint32_t)n, lr, s, loss, grads);
 }
 
 paf_status paf_mlp_train(paf_ctx* ctx, const float* features, const uint16_t* labels, uint64_t n, uint32_t epochs,
@@ -1407,7 +1486,7 @@ paf_status paf_mlp_train(paf_ctx* ctx, const float* features, const uint16_t* la
         for (uint64_t b = 0; b < nb && st == PAF_OK; ++b) {
             const uint64_t a = b * batch;
             const uint32_t k = (uint32_t)std::min<uint64_t>(batch, n - a);
-            st = train_step(ctx, features + a * kFeat, tg + a, k, lr, s, lbuf + ep * nb + b);
+            st = train_step(ctx, features + a * kFeat, tg + a, k, lr, s, lbuf + ep * nb + b, nullptr);
         }
     if (st == PAF_OK && epoch_loss) {
         std::vector<float> h(nb * epochs);

@@ -139,7 +139,7 @@ struct MlpDev {
     uint16_t* w2f = nullptr;  // W2 in fragment order, K permuted [8][4][64][8]
     // training workspace
     void* ws = nullptr;
-    size_t ws_rows = 0;       // padded batch rows the workspace holds
+    size_t ws_splits = 0;     // partial gradients the workspace holds
     int step = 0;
 };
 size_t bucket_count_words(uint64_t n);
