@@ -362,6 +362,7 @@ paf_status paf_destroy(paf_ctx* ctx) {
     if (ctx->scratch_ev) (void)hipEventDestroy(ctx->scratch_ev);
     hipFree(ctx->d_err);
     mlp_free(ctx->mlp);
+    stream_ws_free(ctx->stream_ws);
     hipFree(ctx->ws_pred);
     hipFree(ctx->ws_perm);
     hipFree(ctx->ws_hist);

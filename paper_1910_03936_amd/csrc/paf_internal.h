@@ -152,6 +152,10 @@ hipError_t launch_bucket_sort(const uint8_t* bucket, uint64_t n, uint32_t* count
 hipError_t mlp_alloc(MlpDev& m);
 void mlp_free(MlpDev& m);
 hipError_t mlp_round_weights(MlpDev& m, hipStream_t s);
+
+// stream.hip: what a context keeps between streamed batches.
+struct StreamWs;
+void stream_ws_free(StreamWs* w);
 }  // namespace paf
 
 struct paf_ctx {
@@ -178,6 +182,7 @@ struct paf_ctx {
     uint32_t* ws_counts = nullptr;
     uint32_t* ws_hist = nullptr;
     uint64_t ws_cap = 0;
+    paf::StreamWs* stream_ws = nullptr;
     // Device address of paf_filter_magnet_noalloc's static workspace on this
     // context's device (NULL if the lookup failed, with its error).
     uint8_t* magnet_scratch = nullptr;
