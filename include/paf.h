@@ -158,10 +158,10 @@ paf_status paf_pack_ascii(const char* seqs, uint32_t row_stride, const uint16_t*
  * pass of 3 windows, then 1; above: the same with a first pass of 4; unless
  * a layout was forced with paf_set_layout,
  * whose waves_per_block, chunk_tiles and pass widths then apply here too;
- * chunk_tiles = 0 selects the per-tile engine).  Several stages share one
- * map and one launch up to max_E 7; from max_E 8 SneakySnake runs as above in a launch of its own,
- * and from max_E 15 GateKeeper and Shouji get a launch each too (all on
- * `stream`, in order; the outputs are the same either way). */
+ * chunk_tiles = 0 selects the per-tile engine).  GateKeeper and Shouji share
+ * one map and one launch; SneakySnake joins them up to max_E 2 and runs as
+ * above in a launch of its own from max_E 3 (all on `stream`, in order; the
+ * outputs are the same either way). */
 paf_status paf_filter(paf_ctx* ctx, const paf_batch* batch, uint32_t filters, const paf_out* out,
                       void* stream);
 

@@ -217,7 +217,7 @@ paf_status run_persistent(paf_ctx* ctx, FilterParams p, Engine eng, int emax, co
                           hipStream_t stream, bool use_graph) {
     // Per-pair lengths, thresholds, offsets or an order need the general
     // kernels; a uniform batch in place takes the plain ones.
-    const bool general = p.len || p.E || p.word_offset || p.perm;
+    const bool general = general_batch(p, eng, emax);
     // SneakySnake alone with a chunk size: the compacting engine (one or two
     // lanes per pair); its queue and grid count chunks instead of tiles.
     paf_status st = PAF_OK;
@@ -531,32 +531,20 @@ paf_status paf_filter(paf_ctx* ctx, const paf_batch* batch, uint32_t filters, co
     if ((st = check_out(out, filters)) != PAF_OK) return st;
     const int emax = emax_bucket((int)p.max_E);
     if (emax < 0) return fail(PAF_ERR_RANGE, "max_E exceeds PAF_MAX_E");
-    // Several stages: one map for all of them up to max_E 7.  From 8 on,
-    // SneakySnake runs on its own compacting engine (faster than its share
-    // of the whole-map kernel), and from 15 on GateKeeper and Shouji get a
-    // kernel each (the combined kernel's per-lane state no longer fits at a
-    // useful occupancy).  Every launch writes only its own stages' outputs.
-    const bool several = (filters & (filters - 1u)) != 0u;
-    if (several && (emax >= 15 || (emax >= 8 && (filters & PAF_SNEAKYSNAKE)))) {
-        // Each group below is a single stage, or GateKeeper and Shouji
-        // together under max_E 15, which the test above does not split again.
-        const uint32_t rest = filters & ~(uint32_t)PAF_SNEAKYSNAKE;
-        uint32_t groups[3];
-        int ng = 0;
-        if (filters & PAF_SNEAKYSNAKE) groups[ng++] = PAF_SNEAKYSNAKE;
-        if (emax >= 15) {
-            if (rest & PAF_GATEKEEPER) groups[ng++] = PAF_GATEKEEPER;
-            if (rest & PAF_SHOUJI) groups[ng++] = PAF_SHOUJI;
-        } else if (rest) {
-            groups[ng++] = rest;
-        }
-        for (int i = 0; i < ng; ++i)
-            if ((st = paf_filter(ctx, batch, groups[i], out, stream)) != PAF_OK) return st;
-        return PAF_OK;
+    // Several stages: GateKeeper and Shouji share one map and one launch;
+    // SneakySnake joins them up to max_E 2 and runs on its own engine in a
+    // launch of its own above (all three on 2M pairs of 250 bp, joined and
+    // apart: 189 and 196 us at E = 2, 289 and 262 at E = 5, 364 and 322 at 7).
+    // GateKeeper and Shouji apart were slower at every E (2M pairs, E = 10:
+    // 376 us against 282; E = 25: 804 against 619).
+    const uint32_t rest = filters & ~(uint32_t)PAF_SNEAKYSNAKE;
+    if ((filters & PAF_SNEAKYSNAKE) && rest && emax >= 3) {
+        if ((st = paf_filter(ctx, batch, PAF_SNEAKYSNAKE, out, stream)) != PAF_OK) return st;
+        return paf_filter(ctx, batch, rest, out, stream);
     }
     set_outputs(p, out);
-    const bool general = batch->len || batch->E || batch->word_offset;
     Engine eng = engine_for(filters);
+    const bool general = general_batch(p, eng, emax);
     LaunchShape sh;
     sh.waves_per_block = p.wmax > 8 ? 2 : 4;
     sh.lds_bytes = filter_lds_bytes(sh.waves_per_block, p.wmax);

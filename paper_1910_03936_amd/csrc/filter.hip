@@ -901,6 +901,10 @@ int emax_bucket(int max_E) {
     return -1;
 }
 
+bool general_batch(const FilterParams& p, Engine eng, int emax) {
+    return p.len || p.E || p.word_offset || p.perm || (eng == Engine::Whole && (int)p.uniform_E <= emax_below(emax));
+}
+
 const void* filter_kernel_ptr(Engine eng, bool general, int emax, uint32_t filters) {
     if (eng == Engine::Chunk) return general ? chunk_kernel_for<true, false>(emax) : chunk_kernel_for<false, false>(emax);
     if (eng == Engine::Chunk2) return general ? chunk2_kernel_for<true>(emax) : chunk2_kernel_for<false>(emax);

@@ -37,14 +37,6 @@ constexpr uint32_t kFlowTiles = 16384;
 constexpr uint32_t kRing = 1024;   // counts a wave holds in LDS until their tile is complete
 constexpr uint32_t kMeta = 128;    // GENERAL: pairs whose offset, length and threshold are staged ahead
 
-// Largest threshold class below EMAX.
-constexpr int emax_below(int emax) {
-    int b = -1;
-    for (int e : kEmaxList)
-        if (e < emax) b = e;
-    return b;
-}
-
 __device__ __forceinline__ uint32_t or_xor(uint32_t a, uint32_t t, uint32_t b) {   // t | (a ^ b)
     return __builtin_amdgcn_bitop3_b32(a, t, b, 0xDE);
 }

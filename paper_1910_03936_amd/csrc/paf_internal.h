@@ -89,6 +89,11 @@ struct ScratchScope {
 
 // filter.hip
 int emax_bucket(int max_E);  // smallest instantiated EMAX >= max_E, or -1
+// Whether a launch needs the general kernels: per-pair lengths, thresholds,
+// offsets or an order; and on the whole-map engine a threshold that belongs to
+// a class below emax (its uniform kernels mask only the diagonals between their
+// class and the one below).
+bool general_batch(const FilterParams& p, Engine eng, int emax);
 hipError_t launch_filter(const FilterParams& p, Engine eng, bool general, int emax,
                          const LaunchShape& shape, hipStream_t stream);
 hipError_t launch_pack(const uint8_t* codes, uint32_t code_stride, const uint16_t* len,

@@ -14,6 +14,14 @@ namespace {
 
 constexpr int kEmaxList[] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 15, 20, 25, 31};
 
+// Largest threshold class below EMAX.
+constexpr int emax_below(int emax) {
+    int b = -1;
+    for (int e : kEmaxList)
+        if (e < emax) b = e;
+    return b;
+}
+
 template <int EMAX>
 struct DeadMask {
     using T = typename std::conditional<(2 * EMAX + 1 <= 32), uint32_t, uint64_t>::type;
@@ -159,16 +167,6 @@ __device__ __forceinline__ void build_snake_map(const WindowWords& q, bool bound
         M[I] = x;
         build_snake_map<EMAX, I + 1>(q, boundary, M);
     }
-}
-
-// Whole-map engine: blocked map for SneakySnake/Shouji (vacant and past-end
-// cells are 1) and GateKeeper's map (vacant and past-end cells are 0).
-template <int d>
-__device__ __forceinline__ void diag_both(const WindowWords& q, uint32_t& Mh, uint32_t& G) {
-    const uint32_t x = diag_raw<d>(q);
-    const uint32_t v = diag_vacant<d>(q);
-    Mh = x | v | q.vc;          // q.vc doubles as "column >= m" for this window
-    G = x & ~v & ~q.vc;
 }
 
 // ---------------------------------------------------------------------------

@@ -9,162 +9,229 @@ namespace paf {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Whole-map engine.
+// Whole-map engine.  The raw mismatch words of the current and the next window
+// are kept; vacant and past-end cells are folded in (blocked for SneakySnake
+// and Shouji, free for GateKeeper) only in the windows that hold any.
+//
+// Bound by VALU issue, where adds, shifts right and logic (v_bitop3 on
+// registers included) take about 2.4 cycles a wave and funnel shifts, shifts
+// left, field extracts and compares about 4.3: the diagonals are worked on with
+// as few of the latter as the definitions allow.  2M pairs of 250 bp at E = 10:
+// GateKeeper 148 -> 112 us (opening once a window instead of amending every
+// diagonal), Shouji 400 -> 264 us (eight ranks instead of a ones count, and the
+// store by table look-up instead of ten instructions a column), the two
+// together 543 -> 282 us (one set of raw words instead of a map each, which
+// had left two waves per SIMD).
 
-
-// Shouji: bit-sliced best 4-column segment per window start column.
-struct ShoujiBest {
-    uint32_t o0, o1, o2;      // ones in the best segment (bit-sliced, 0..4)
-    uint32_t b0, b1, b2, b3;  // the best segment's bits
-};
-
-// Three-input logic in one v_bitop3 each (truth table bit s0 * 4 + s1 * 2 + s2):
-// m ? x : y; a ^ b ^ c; and one step of a bit-sliced less-than from the low
-// bit up, (~n & o) | (~(n ^ o) & t).
-__device__ __forceinline__ uint32_t sel3(uint32_t m, uint32_t x, uint32_t y) {
+// Three-input logic in one v_bitop3 each (truth table bit s0 * 4 + s1 * 2 + s2).
+__device__ __forceinline__ uint32_t sel3(uint32_t m, uint32_t x, uint32_t y) {   // m ? x : y
     return __builtin_amdgcn_bitop3_b32(m, x, y, 0xCA);
 }
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
+__device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);
+}
+__device__ __forceinline__ uint32_t or3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0xFE);
+}
+// One step of a bit-sliced less-than from the low bit up, (~n & o) | (~(n ^ o) & t).
 __device__ __forceinline__ uint32_t lt_step(uint32_t n, uint32_t o, uint32_t t) {
     return __builtin_amdgcn_bitop3_b32(n, o, t, 0x8E);
 }
+__device__ __forceinline__ uint32_t or_and(uint32_t a, uint32_t b, uint32_t c) {   // (a | b) & c
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0xA8);
+}
 
-__device__ __forceinline__ void shouji_candidate(ShoujiBest& bs, uint32_t cur, uint32_t nxt,
-                                                 bool first) {
-    const uint32_t B0 = cur;
+// Shouji's best 4-column segment at each of the window's 32 start columns,
+// bit-sliced.  A segment of bits b0..b3 (b0: its first column) with r ones in
+// b1..b3 is ranked by 2 (r + b0) + b0: fewer ones first, and on a tie a
+// segment that starts with a zero.  That key takes eight values, so its rank
+// k (k2 k1 k0) is three functions of b0 and r; b0 and r's low bit are
+// functions of k again, and b3 is the parity that is left.
+struct ShoujiBest {
+    uint32_t k0, k1, k2, b1, b2;
+};
+
+__device__ __forceinline__ void shouji_candidate(ShoujiBest& bs, uint32_t cur, uint32_t nxt, bool first) {
     const uint32_t B1 = funnel(nxt, cur, 1);
     const uint32_t B2 = funnel(nxt, cur, 2);
     const uint32_t B3 = funnel(nxt, cur, 3);
-    // Ones in the segment, bit-sliced: n = B0 + B1 + B2 + B3 (0..4).
-    const uint32_t s01 = B0 ^ B1, c01 = B0 & B1, s23 = B2 ^ B3, c23 = B2 & B3;
-    const uint32_t n0 = s01 ^ s23;
-    const uint32_t n1 = xor3(c01, c23, s01 & s23);
-    const uint32_t n2 = c01 & c23;
+    const uint32_t r0 = xor3(B1, B2, B3), r1 = maj3(B1, B2, B3);
+    const uint32_t k2 = maj3(cur, r1, r0);
+    const uint32_t k1 = __builtin_amdgcn_bitop3_b32(cur, r1, r0, 0xD4);
+    const uint32_t k0 = __builtin_amdgcn_bitop3_b32(cur, r1, r0, 0x8E);
     if (first) {
-        bs = {n0, n1, n2, B0, B1, B2, B3};
+        bs = {k0, k1, k2, B1, B2};
         return;
     }
-    // Fewer ones wins; on a tie, a segment that starts with a zero beats one
-    // that does not; otherwise the earlier diagonal is kept.  That is one
-    // strict comparison of the keys 2 n + B0 and 2 o + b0, bit-sliced from
-    // the lowest bit up: t = new < best on the bits seen so far.
-    const uint32_t t0 = ~B0 & bs.b0;
-    const uint32_t rep = lt_step(n2, bs.o2, lt_step(n1, bs.o1, lt_step(n0, bs.o0, t0)));
-    bs.o0 = sel3(rep, n0, bs.o0);
-    bs.o1 = sel3(rep, n1, bs.o1);
-    bs.o2 = sel3(rep, n2, bs.o2);
-    bs.b0 = sel3(rep, B0, bs.b0);
+    // Equal ranks keep the earlier diagonal.
+    const uint32_t rep = lt_step(k2, bs.k2, lt_step(k1, bs.k1, ~k0 & bs.k0));
+    bs.k0 = sel3(rep, k0, bs.k0);
+    bs.k1 = sel3(rep, k1, bs.k1);
+    bs.k2 = sel3(rep, k2, bs.k2);
     bs.b1 = sel3(rep, B1, bs.b1);
     bs.b2 = sel3(rep, B2, bs.b2);
-    bs.b3 = sel3(rep, B3, bs.b3);
 }
 
-// Bits 0..7 of x spread to bits 0, 4, ..., 28.
-__device__ __forceinline__ uint32_t spread8(uint32_t x) {
-    x = (x | (x << 12)) & 0x000F000Fu;
-    x = (x | (x << 6)) & 0x03030303u;
-    return (x | (x << 3)) & 0x11111111u;
-}
-
-// The best segments of the window's 32 start columns as nibbles: word k holds
-// the segment of column j = 8k + i in bits 4i..4i+3 (bit t = the segment's
-// column j + t).
-__device__ __forceinline__ void shouji_nibbles(const ShoujiBest& bs, uint32_t* nib) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int sh = 8 * k;
-        nib[k] = spread8((bs.b0 >> sh) & 0xFFu) | (spread8((bs.b1 >> sh) & 0xFFu) << 1) |
-                 (spread8((bs.b2 >> sh) & 0xFFu) << 2) | (spread8((bs.b3 >> sh) & 0xFFu) << 3);
-    }
-}
-
-// Sequential store into the Shouji bit-vector for the 32 windows starting in
-// this window (Sec. 6.2.2): the best segment overwrites the vector's four
-// bits when it holds strictly more zeros.  S covers columns [32w, 32w+64).
-// Window starts past the pair's end hold segment 1111 (see below), which
-// never holds strictly more zeros than the vector, so they store nothing.
-template <int J = 0>
-__device__ __forceinline__ void shouji_store_nib(const uint32_t* nib, uint32_t& S_lo, uint32_t& S_hi) {
-    if constexpr (J < 32) {
-        const uint32_t V = (nib[J >> 3] >> (4 * (J & 7))) & 0xFu;
-        uint32_t cur;
-        if constexpr (J <= 28) cur = (S_lo >> J) & 0xFu;
-        else cur = funnel(S_hi, S_lo, J) & 0xFu;
-        const bool take = popc(V) < popc(cur);
-        if constexpr (J <= 28) {
-            const uint32_t nlo = (S_lo & ~(0xFu << J)) | (V << J);
-            S_lo = take ? nlo : S_lo;
-        } else {
-            const uint32_t nlo = (S_lo & ~(0xFu << J)) | (V << J);
-            const uint32_t nhi = (S_hi & ~(0xFu >> (32 - J))) | (V >> (32 - J));
-            S_lo = take ? nlo : S_lo;
-            S_hi = take ? nhi : S_hi;
+// Shouji's sequential store (Sec. 6.2.2): the best segment V of column j
+// overwrites the vector's bits j..j+3 when it holds strictly more zeros.  Bit
+// j + 3 is still 1 then, so the vector's bits j..j+2 are the whole state s,
+// and the column is an automaton: V is taken when popc(V) <= popc(s); the
+// column's final bit is V's (s's) lowest, and the next state is V >> 1 (s >> 1
+// with a 1 on top).  Two columns go through one table look-up: entry (V pair,
+// s) holds the next state times two in its low bits and 256 times the ones
+// the two columns add to the count.  A V pair is a byte with bit t (2 p + t)
+// of column t's segment bit p.
+struct alignas(16) ShoujiTable {
+    uint16_t e[256 * 8];
+};
+constexpr ShoujiTable make_shouji_table() {
+    ShoujiTable T{};
+    for (uint32_t v = 0; v < 256; ++v)
+        for (uint32_t s0 = 0; s0 < 8; ++s0) {
+            uint32_t s = s0, ones = 0;
+            for (uint32_t t = 0; t < 2; ++t) {
+                uint32_t V = 0, nv = 0;
+                for (uint32_t p = 0; p < 4; ++p) V |= ((v >> (2 * p + t)) & 1u) << p;
+                for (uint32_t p = 0; p < 4; ++p) nv += (V >> p) & 1u;
+                const uint32_t ns = (s & 1u) + ((s >> 1) & 1u) + (s >> 2);
+                const bool take = nv <= ns;
+                ones += take ? V & 1u : s & 1u;
+                s = take ? V >> 1 : (s >> 1) | 4u;
+            }
+            T.e[v * 8 + s0] = (uint16_t)(2u * s | ones << 8);
         }
-        shouji_store_nib<J + 1>(nib, S_lo, S_hi);
-    }
+    return T;
+}
+__device__ const ShoujiTable kShoujiTable = make_shouji_table();
+
+// V pairs of columns 8 q .. 8 q + 7 (a byte per two columns) from the planes.
+__device__ __forceinline__ uint32_t shouji_pairs(int q, uint32_t b0, uint32_t b1, uint32_t b2, uint32_t b3) {
+    auto spread = [q](uint32_t b) {
+        uint32_t x = (b << (24 - 8 * q)) & 0xFF000000u;
+        x = or_and(x, x >> 12, 0xF000F000u);
+        return or_and(x, x >> 6, 0xC0C0C0C0u);
+    };
+    return or3(spread(b0) >> 6, spread(b1) >> 4, spread(b2) >> 2) | spread(b3);
 }
 
-template <int EMAX, int I = 0>
-__device__ __forceinline__ void build_both(const WindowWords& q, uint32_t* Mh, uint32_t* G) {
+// The window's 32 columns through the table: the ones they add, `state` (times
+// two) carried on.
+__device__ __forceinline__ uint32_t shouji_store(const uint16_t* table, const ShoujiBest& bs, uint32_t past, uint32_t& state) {
+    const uint32_t b0 = __builtin_amdgcn_bitop3_b32(bs.k2, bs.k1, bs.k0, 0xD4) | past;
+    const uint32_t r0 = __builtin_amdgcn_bitop3_b32(bs.k2, bs.k1, bs.k0, 0xB2);
+    const uint32_t b3 = xor3(r0, bs.b1, bs.b2) | past;
+    const uint32_t b1 = bs.b1 | past, b2 = bs.b2 | past;
+    const char* tab = reinterpret_cast<const char*>(table);
+    uint32_t total = 0, r = state;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t w = shouji_pairs(q, b0, b1, b2, b3);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint32_t v = (t == 0 ? w << 4 : w >> (8 * t - 4)) & 0xFF0u;
+            r = *reinterpret_cast<const uint16_t*>(tab + (v | (r & 0xEu)));
+            total += r;   // the states add up to less than 256
+        }
+    }
+    state = r & 0xEu;
+    return total >> 8;
+}
+
+// Raw mismatch words of a window; diagonals beyond the pair's threshold are
+// all ones (the ones that can lie beyond it, see over_E).
+template <int EMAX, bool GENERAL>
+__host__ __device__ constexpr bool may_exceed(int ad) {
+    return GENERAL ? ad > 0 : ad > emax_below(EMAX) + 1;
+}
+__device__ __forceinline__ uint32_t over_E(uint32_t E, int ad) { return (uint32_t)((int32_t)(E - (uint32_t)ad) >> 31); }
+
+template <int EMAX, bool GENERAL, int I = 0>
+__device__ __forceinline__ void build_raw(const WindowWords& q, uint32_t E, uint32_t* R) {
     if constexpr (I < 2 * EMAX + 1) {
-        diag_both<I - EMAX>(q, Mh[I], G[I]);
-        build_both<EMAX, I + 1>(q, Mh, G);
+        constexpr int d = I - EMAX, ad = d < 0 ? -d : d;
+        R[I] = diag_raw<d>(q);
+        if constexpr (may_exceed<EMAX, GENERAL>(ad)) R[I] |= over_E(E, ad);
+        build_raw<EMAX, GENERAL, I + 1>(q, E, R);
     }
 }
 
-// Only the blocked map (SneakySnake, Shouji): vacant and past-end cells 1.
-template <int EMAX, int I = 0>
-__device__ __forceinline__ void build_blocked(const WindowWords& q, uint32_t* Mh) {
+// Vacant and past-end cells of a window (none on the diagonals beyond the
+// threshold, whose words are ones for every stage).
+struct Vacancy {
+    uint32_t vp, vc, vn;
+};
+__device__ __forceinline__ Vacancy vacancy_of(int k, int m) {
+    return Vacancy{vacant_word(k - 1, m), vacant_word(k, m), vacant_word(k + 1, m)};
+}
+template <int d, bool MASK>
+__device__ __forceinline__ uint32_t diag_blank(const Vacancy& v, uint32_t E) {
+    uint32_t x = v.vc;
+    if constexpr (d > 0) x |= funnel(v.vn, v.vc, d);
+    if constexpr (d < 0) x |= funnel(v.vc, v.vp, 32 + d);
+    if constexpr (MASK) x &= ~over_E(E, d < 0 ? -d : d);
+    return x;
+}
+
+// GateKeeper (Ch. 5, Sec. 5.2.2): the amendment turns streaks of one or two
+// zeros into ones, which leaves the zeros that lie in a run of three or more
+// (beyond the map's ends all cells count as zero).  The masks are AND-ed, so a
+// result bit is zero when some diagonal keeps a zero there; since taking the
+// cells that a run covers commutes with that, each diagonal only gives the
+// starts of its runs of three, not (g | g1 | g2), and the runs grow back to
+// their cells once a window, over all diagonals together: four instructions a
+// diagonal instead of seven.  Shouji's candidates share the same words.
+template <int EMAX, bool GENERAL, bool INNER, bool GKS, bool SHS, int I = 0>
+__device__ __forceinline__ void whole_diagonals(const uint32_t* Rc, const uint32_t* Rn, const Vacancy& vc, const Vacancy& vn,
+                                                uint32_t E, uint32_t& starts, ShoujiBest& bs) {
     if constexpr (I < 2 * EMAX + 1) {
-        constexpr int d = I - EMAX;
-        Mh[I] = diag_raw<d>(q) | diag_vacant<d>(q) | q.vc;
-        build_blocked<EMAX, I + 1>(q, Mh);
+        constexpr int d = I - EMAX, ad = d < 0 ? -d : d;
+        constexpr bool MASK = may_exceed<EMAX, GENERAL>(ad);
+        const uint32_t c = Rc[I], n = Rn[I];
+        uint32_t bc = 0, bn = 0;
+        if constexpr (!INNER) {
+            bc = diag_blank<d, MASK>(vc, E);
+            bn = diag_blank<d, MASK>(vn, E);
+        }
+        if constexpr (GKS) {
+            const uint32_t gc = c & ~bc, gn = n & ~bn;
+            starts &= or3(gc, funnel(gn, gc, 1), funnel(gn, gc, 2));
+        }
+        if constexpr (SHS && EMAX > 0) shouji_candidate(bs, c | bc, n | bn, I == 0);
+        whole_diagonals<EMAX, GENERAL, INNER, GKS, SHS, I + 1>(Rc, Rn, vc, vn, E, starts, bs);
     }
 }
 
-// Window k of every active lane's pair is inner: k >= 1 and its columns,
-// plus max_E beyond, lie before the pair's end, so no cell of any diagonal
-// is vacant there.
-template <int EMAX>
-__device__ __forceinline__ bool inner_window(bool active, uint32_t k, uint32_t m) {
-    return !wave_any(active && (k == 0u || 32u * (k + 1u) + (uint32_t)EMAX > m));
-}
-
-// Only GateKeeper's map: vacant and past-end cells 0 (INNER: an inner window,
-// the raw mismatch words).
-template <int EMAX, bool INNER = false, int I = 0>
-__device__ __forceinline__ void build_gk(const WindowWords& q, uint32_t* G) {
+// SneakySnake's map of a window: vacant and past-end cells blocked.
+template <int EMAX, bool GENERAL, int I = 0>
+__device__ __forceinline__ void blocked_words(const uint32_t* R, const Vacancy& v, uint32_t E, uint32_t* M) {
     if constexpr (I < 2 * EMAX + 1) {
-        constexpr int d = I - EMAX;
-        if constexpr (INNER) G[I] = diag_raw<d>(q);
-        else G[I] = diag_raw<d>(q) & ~(diag_vacant<d>(q) | q.vc);
-        build_gk<EMAX, INNER, I + 1>(q, G);
+        constexpr int d = I - EMAX, ad = d < 0 ? -d : d;
+        M[I] = R[I] | diag_blank<d, may_exceed<EMAX, GENERAL>(ad)>(v, E);
+        blocked_words<EMAX, GENERAL, I + 1>(R, v, E, M);
     }
 }
 
-// Fw AND GateKeeper's amendment of one window word g (Ch. 5, Sec. 5.2.2; SRS
-// of Sec. 3.2.1): a zero inside a streak of one or two zeros bounded by ones
-// on both sides becomes one.  L1/L2 are the bits one/two columns to the left,
-// R1/R2 to the right (taken from the neighbouring windows); the amended word
-// g | L1 (R1 | R2) | R1 (L1 | L2) = L1 (R1 | R2) | (R1 L2 | g) takes three
-// 3-input operations with the AND.
-__device__ __forceinline__ uint32_t and_amended(uint32_t Fw, uint32_t g, uint32_t prev, uint32_t next) {
-    const uint32_t L1 = funnel(g, prev, 31);
-    const uint32_t L2 = funnel(g, prev, 30);
-    const uint32_t R1 = funnel(next, g, 1);
-    const uint32_t R2 = funnel(next, g, 2);
-    const uint32_t t = __builtin_amdgcn_bitop3_b32(L1, R1, R2, 0xE0);  // L1 & (R1 | R2)
-    const uint32_t u = __builtin_amdgcn_bitop3_b32(R1, L2, g, 0xEA);   // (R1 & L2) | g
-    return __builtin_amdgcn_bitop3_b32(Fw, t, u, 0xE0);                // Fw & (t | u)
+// The starts of runs of three zeros in the two columns before the first: their
+// runs reach column 0 (all of it free on some diagonal, or columns 0 and 1).
+template <int EMAX, bool GENERAL, int I = 0>
+__device__ __forceinline__ void left_starts(const uint32_t* R, const Vacancy& v, uint32_t E, uint32_t& one, uint32_t& two) {
+    if constexpr (I < 2 * EMAX + 1) {
+        constexpr int d = I - EMAX, ad = d < 0 ? -d : d;
+        const uint32_t g = R[I] & ~diag_blank<d, may_exceed<EMAX, GENERAL>(ad)>(v, E);
+        one &= g;
+        two &= g | (g >> 1);
+        left_starts<EMAX, GENERAL, I + 1>(R, v, E, one, two);
+    }
 }
 
 // FS: the decision stages this instantiation runs (bits of PAF_*), or 0 for
-// any mask given at run time.  Only the words the stages read are built.
+// any mask given at run time.
 template <int EMAX, bool GENERAL, int FS>
-__device__ void whole_tile(const FilterParams& P, uint64_t tile, int lane, uint64_t* rdL,
-                           uint64_t* rfL) {
+__device__ void whole_tile(const FilterParams& P, uint64_t tile, int lane, uint64_t* rdL, uint64_t* rfL,
+                           const uint16_t* table) {
     constexpr int D = 2 * EMAX + 1;
     using DT = typename DeadMask<EMAX>::T;
     uint64_t off;
@@ -172,121 +239,71 @@ __device__ void whole_tile(const FilterParams& P, uint64_t tile, int lane, uint6
     stage_tile<GENERAL>(P, tile, lane, ps, off, rdL, rfL);
 
     constexpr bool RT = FS == 0;
-    constexpr bool needG = RT || (FS & PAF_GATEKEEPER);
-    constexpr bool needM = RT || (FS & (PAF_SNEAKYSNAKE | PAF_SHOUJI));
-    const bool doSS = RT ? (P.filters & PAF_SNEAKYSNAKE) != 0 : (FS & PAF_SNEAKYSNAKE) != 0;
-    const bool doGK = RT ? (P.filters & PAF_GATEKEEPER) != 0 : (FS & PAF_GATEKEEPER) != 0;
-    const bool doSH = RT ? (P.filters & PAF_SHOUJI) != 0 : (FS & PAF_SHOUJI) != 0;
+    constexpr bool GKS = RT || (FS & PAF_GATEKEEPER), SHS = RT || (FS & PAF_SHOUJI), SSS = RT;
+    const bool doSS = RT && (P.filters & PAF_SNEAKYSNAKE) != 0;
+    const bool doGK = RT ? (P.filters & PAF_GATEKEEPER) != 0 : GKS;
+    const bool doSH = RT ? (P.filters & PAF_SHOUJI) != 0 : SHS;
     const uint32_t m = ps.m, E = ps.E;
-    const bool mask_E = GENERAL ? (P.E != nullptr || P.uniform_E < (uint32_t)EMAX)
-                                : (P.uniform_E < (uint32_t)EMAX);
 
     Snake z{0u, 0u, ps.valid && doSS, false, 0u};
     bool cont = false;
     DT dead = 0;
-    uint32_t gk_ham = 0, gk_cnt = 0;
-    uint32_t S_lo = ~0u, S_hi = ~0u, sh_cnt = 0;
+    uint32_t gk_ham = 0, gk_cnt = 0, prev_starts = 0;
+    uint32_t sh_cnt = 0, sh_state = 7u << 1;
 
-    uint32_t Mc[needM ? D : 1], Gc[needG ? D : 1], Gp[needG ? D : 1];
-    if (ps.valid) {
+    uint32_t Ra[D], Rb[D];
+    {
         const WindowWords q = window_words(rdL, rfL, lane, 0, P.wmax, (int)m);
-        if constexpr (needM && needG) build_both<EMAX>(q, Mc, Gc);
-        else if constexpr (needM) build_blocked<EMAX>(q, Mc);
-        else build_gk<EMAX>(q, Gc);
-    }
-    if constexpr (needG) {
-#pragma unroll
-        for (int i = 0; i < D; ++i) Gp[i] = 0u;
-    }
-    if (mask_E && ps.valid) {
-#pragma unroll
-        for (int i = 0; i < D; ++i) {
-            const int d = i - EMAX;
-            if ((uint32_t)(d < 0 ? -d : d) > E) {
-                if constexpr (needM) Mc[i] = ~0u;
-                if constexpr (needG) { Gc[i] = ~0u; Gp[i] = ~0u; }
-            }
+        build_raw<EMAX, GENERAL>(q, E, Ra);
+        if (GKS && doGK) {
+            uint32_t one = ~0u, two = ~0u;
+            left_starts<EMAX, GENERAL>(Ra, vacancy_of(0, (int)m), E, one, two);
+            prev_starts = (~one & 1u) << 30 | (~two & 1u) << 31;
         }
     }
-
-    if constexpr (FS == PAF_GATEKEEPER && EMAX <= 10) {
-        // GateKeeper alone: the previous, current and next window's masks
-        // take turns in three arrays, so no window copies them on (the loop
-        // is unrolled by hand; its wave vote keeps the compiler from it).
-        // Above max_E 10 the third array would cost occupancy.
-        uint32_t Gx[D];
-        auto gk_window = [&](uint32_t w, const uint32_t (&Gpv)[D], const uint32_t (&Gcu)[D], uint32_t (&Gnx)[D]) {
-            const bool inner = inner_window<EMAX>(ps.valid && w < ps.W, w + 1u, m);
-            if (ps.valid && w < ps.W) {
-                const uint32_t colpast = vacant_word((int)w, (int)m);  // columns >= m
-                gk_ham += popc(Gcu[EMAX] & ~colpast);
-                const WindowWords qn = window_words(rdL, rfL, lane, (int)w + 1, P.wmax, (int)m);
-                if (inner) build_gk<EMAX, true>(qn, Gnx);
-                else build_gk<EMAX>(qn, Gnx);
-                uint32_t Fw = ~0u;
-#pragma unroll
-                for (int i = 0; i < D; ++i) {
-                    if (mask_E) {
-                        const int d = i - EMAX;
-                        if ((uint32_t)(d < 0 ? -d : d) > E) Gnx[i] = ~0u;
-                    }
-                    Fw = and_amended(Fw, Gcu[i], Gpv[i], Gnx[i]);
-                }
-                gk_cnt += popc(Fw & ~colpast);
-            }
-        };
-        for (uint32_t w = 0;;) {
-            if (!wave_any(ps.valid && w < ps.W)) break;
-            gk_window(w++, Gp, Gc, Gx);
-            if (!wave_any(ps.valid && w < ps.W)) break;
-            gk_window(w++, Gc, Gx, Gp);
-            if (!wave_any(ps.valid && w < ps.W)) break;
-            gk_window(w++, Gx, Gp, Gc);
-        }
-    } else
-    for (uint32_t w = 0; wave_any(ps.valid && w < ps.W); ++w) {
+    // One window: its words in Rc, the next one's built into Rn.  Lanes past
+    // their pair's last window run along (their words are staged as zeros) and
+    // their results are not counted.
+    auto window = [&](uint32_t w, const uint32_t (&Rc)[D], uint32_t (&Rn)[D]) {
         const bool have = ps.valid && w < ps.W;
-        if (have) {
-            const uint32_t colpast = vacant_word((int)w, (int)m);  // columns >= m
-            // SneakySnake on this window.
-            if constexpr (needM)
-                if (doSS && z.act) snake_window<EMAX, DT>(z, Mc, w, m, E, cont, dead);
-            // GateKeeper's fast path: Hamming distance on diagonal 0 (its
-            // mismatches, vacant cells not counted).
-            if constexpr (needG)
-                if (doGK) gk_ham += popc(Gc[EMAX] & ~colpast);
-            // This window's blocked main diagonal (Shouji at E = 0, below).
-            const uint32_t mc0 = needM ? Mc[0] : 0u;
-            // Next window's maps, then GateKeeper and Shouji per diagonal.
-            const WindowWords qn = window_words(rdL, rfL, lane, (int)w + 1, P.wmax, (int)m);
-            uint32_t Fw = ~0u;
-            ShoujiBest bs;
-            uint32_t Mn[needM ? D : 1], Gn[needG ? D : 1];
-            if constexpr (needM && needG) build_both<EMAX>(qn, Mn, Gn);
-            else if constexpr (needM) build_blocked<EMAX>(qn, Mn);
-            else build_gk<EMAX>(qn, Gn);
-#pragma unroll
-            for (int i = 0; i < D; ++i) {
-                if (mask_E) {
-                    const int d = i - EMAX;
-                    if ((uint32_t)(d < 0 ? -d : d) > E) {
-                        if constexpr (needM) Mn[i] = ~0u;
-                        if constexpr (needG) Gn[i] = ~0u;
-                    }
-                }
-                if constexpr (needG) {
-                    if (doGK) Fw = and_amended(Fw, Gc[i], Gp[i], Gn[i]);
-                    Gp[i] = Gc[i];
-                    Gc[i] = Gn[i];
-                }
-                if constexpr (needM) {
-                    if constexpr (EMAX > 0)
-                        if (doSH) shouji_candidate(bs, Mc[i], Mn[i], i == 0);
-                    Mc[i] = Mn[i];
-                }
+        build_raw<EMAX, GENERAL>(window_words(rdL, rfL, lane, (int)w + 1, P.wmax, (int)m), E, Rn);
+        const uint32_t past = have ? vacant_word((int)w, (int)m) : ~0u;   // columns >= m
+        const Vacancy vc = vacancy_of((int)w, (int)m), vn = vacancy_of((int)w + 1, (int)m);
+        // Cells of this window or the next one are vacant only near the ends.
+        const bool inner = !wave_any(have && (w == 0u || 32u * (w + 2u) + (uint32_t)EMAX > m));
+        if constexpr (SSS)
+            if (doSS && have && z.act) {
+                uint32_t M[D];
+                blocked_words<EMAX, GENERAL>(Rc, vc, E, M);
+                snake_window<EMAX, DT>(z, M, w, m, E, cont, dead);
             }
-            if (doGK) gk_cnt += popc(Fw & ~colpast);
-            if (doSH && EMAX == 0) {
+        uint32_t starts = ~0u;
+        ShoujiBest bs;
+        auto diagonals = [&](auto gk, auto sh) {
+            constexpr bool G = decltype(gk)::value, S = decltype(sh)::value;
+            if (inner) whole_diagonals<EMAX, GENERAL, true, G, S>(Rc, Rn, vc, vn, E, starts, bs);
+            else whole_diagonals<EMAX, GENERAL, false, G, S>(Rc, Rn, vc, vn, E, starts, bs);
+        };
+        using yes = std::true_type;
+        using no = std::false_type;
+        if constexpr (!RT) {
+            diagonals(std::integral_constant<bool, GKS>{}, std::integral_constant<bool, SHS>{});
+        } else {
+            if (doGK && doSH) diagonals(yes{}, yes{});
+            else if (doGK) diagonals(yes{}, no{});
+            else if (doSH) diagonals(no{}, yes{});
+        }
+        // The main diagonal's mismatches (never vacant inside the pair).
+        const uint32_t ham = popc(Rc[EMAX] & ~past);
+        if (GKS && doGK) {
+            gk_ham += ham;   // GateKeeper's fast path
+            const uint32_t runs = ~starts;
+            const uint32_t kept = or3(runs, funnel(runs, prev_starts, 31), funnel(runs, prev_starts, 30));
+            gk_cnt += popc(~(kept | past));
+            prev_starts = runs;
+        }
+        if (SHS && doSH) {
+            if constexpr (EMAX == 0) {
                 // One diagonal (E = 0): the window starting at column j
                 // replaces the vector's bits j..j+3, which hold the diagonal's
                 // bits j..j+2 and a still unset 1 at j+3, exactly when bit j+3
@@ -294,23 +311,22 @@ __device__ void whole_tile(const FilterParams& P, uint64_t tile, int lane, uint6
                 // first four bits equal to the diagonal's either way.  So the
                 // vector ends equal to the diagonal, and the count is its
                 // Hamming distance.
-                sh_cnt += popc(mc0 & ~colpast);
-            } else if (doSH) {
-                // Start columns at or past the pair's end get segment 1111.
-                const uint32_t ncols = m - 32u * w;  // >= 1
-                const uint32_t past = ncols >= 32u ? 0u : ~0u << ncols;
-                bs.b0 |= past;
-                bs.b1 |= past;
-                bs.b2 |= past;
-                bs.b3 |= past;
-                uint32_t nib[4];
-                shouji_nibbles(bs, nib);
-                shouji_store_nib(nib, S_lo, S_hi);
-                sh_cnt += popc(S_lo & ~colpast);
-                S_lo = S_hi;
-                S_hi = ~0u;
+                sh_cnt += ham;
+            } else {
+                // Start columns at or past the pair's end get segment 1111,
+                // which never replaces anything.  The vector stays 1 in the
+                // columns past the end, which are not counted.
+                const uint32_t ones = shouji_store(table, bs, past, sh_state);
+                sh_cnt += have ? ones - popc(past) : 0u;
             }
         }
+    };
+    // (two windows a turn, so that no window's words are copied on)
+    for (uint32_t w = 0;; w += 2) {
+        if (!wave_any(ps.valid && w < ps.W)) break;
+        window(w, Ra, Rb);
+        if (!wave_any(ps.valid && w + 1 < ps.W)) break;
+        window(w + 1, Rb, Ra);
     }
 
     const bool gk_acc = gk_ham <= E || gk_cnt <= E;
@@ -334,15 +350,22 @@ __device__ void whole_tile(const FilterParams& P, uint64_t tile, int lane, uint6
     }
 }
 
-
 template <int EMAX, bool GENERAL, int FS>
 __global__ void __launch_bounds__(256) whole_kernel(FilterParams P) {
     extern __shared__ uint64_t lds[];
+    constexpr bool TABLE = EMAX > 0 && (FS == 0 || (FS & PAF_SHOUJI) != 0);
+    __shared__ typename std::conditional<TABLE, ShoujiTable, uint4>::type table;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
+    if constexpr (TABLE) {
+        for (uint32_t i = threadIdx.x; i < sizeof(ShoujiTable) / 16; i += blockDim.x)
+            reinterpret_cast<uint4*>(&table)[i] = reinterpret_cast<const uint4*>(&kShoujiTable)[i];
+        __syncthreads();
+    }
     uint64_t* rdL = lds + (size_t)wave * 2 * P.wmax * kLdsRow;
     uint64_t* rfL = rdL + (size_t)P.wmax * kLdsRow;
-    for_each_tile(P, lane, wave, [&](uint64_t tile) { whole_tile<EMAX, GENERAL, FS>(P, tile, lane, rdL, rfL); });
+    const uint16_t* tab = reinterpret_cast<const uint16_t*>(&table);
+    for_each_tile(P, lane, wave, [&](uint64_t tile) { whole_tile<EMAX, GENERAL, FS>(P, tile, lane, rdL, rfL, tab); });
 }
 
 template <bool GENERAL, int FS>
@@ -360,13 +383,17 @@ const void* whole_for(int emax) {
 
 }  // namespace
 
-// GateKeeper alone and Shouji alone get kernels of their own; every other
-// mask runs on the kernel that reads the mask at run time.
+// GateKeeper, Shouji and the two together get kernels of their own; the masks
+// with SneakySnake run on the kernel that reads the mask at run time.
 const void* whole_kernel_ptr(bool general, int emax, uint32_t filters) {
-    if (filters == PAF_GATEKEEPER) return general ? whole_for<true, PAF_GATEKEEPER>(emax)
-                                                  : whole_for<false, PAF_GATEKEEPER>(emax);
-    if (filters == PAF_SHOUJI) return general ? whole_for<true, PAF_SHOUJI>(emax) : whole_for<false, PAF_SHOUJI>(emax);
-    return general ? whole_for<true, 0>(emax) : whole_for<false, 0>(emax);
+    switch (filters) {
+        case PAF_GATEKEEPER: return general ? whole_for<true, PAF_GATEKEEPER>(emax) : whole_for<false, PAF_GATEKEEPER>(emax);
+        case PAF_SHOUJI: return general ? whole_for<true, PAF_SHOUJI>(emax) : whole_for<false, PAF_SHOUJI>(emax);
+        case PAF_GATEKEEPER | PAF_SHOUJI:
+            return general ? whole_for<true, PAF_GATEKEEPER | PAF_SHOUJI>(emax)
+                           : whole_for<false, PAF_GATEKEEPER | PAF_SHOUJI>(emax);
+        default: return general ? whole_for<true, 0>(emax) : whole_for<false, 0>(emax);
+    }
 }
 
 }  // namespace paf
