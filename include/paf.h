@@ -20,8 +20,8 @@
  *  - A context serves one device; calls on one context from several threads
  *    must be serialized by the caller.
  *  - Calls that use the context's own device memory (the persistent launch's
- *    work-queue counter, the bucketing workspace of the bucketed and MAGNET
- *    calls, the cost model's weights and training workspace) may be made on
+ *    work-queue counter, the bucketing workspace of the bucketed calls, the
+ *    cost model's weights and training workspace) may be made on
  *    different streams: the library orders them, a call on another stream
  *    than the previous such call waiting on the device for that call's work
  *    (an event the context records).  paf_filter, paf_filter_partitioned,
@@ -199,25 +199,18 @@ paf_status paf_filter_partitioned(paf_ctx* ctx, const paf_batch* batch, uint32_t
  * count = min(m - columns covered by the runs, E+1), accept = count <= E
  * (the thesis rejects when the runs cover fewer than m - E columns).  Unlike
  * SneakySnake, MAGNET may reject a pair within E edits (Sec. 9.3.3).  Writes
- * out->accept_bits[0] and out->count[0] (the other slots are ignored).  Uses
- * the context's bucketing workspace (5 bytes per pair, grown on first use
- * with a larger batch). */
+ * out->accept_bits[0] and out->count[0] (the other slots are ignored).  Runs
+ * SneakySnake into them first and MAGNET on the pairs it accepts (it accepts
+ * every pair that MAGNET accepts); needs no workspace. */
 paf_status paf_filter_magnet(paf_ctx* ctx, const paf_batch* batch, const paf_out* out, void* stream);
 
-/* paf_filter_magnet without any allocation, for callers that cannot allocate
- * device memory: code under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc.  Same arguments and outputs as paf_filter_magnet.
- * Its workspace is not the context's: it is a static device array of the
- * library, laid out for up to PAF_MAGNET_NOALLOC_MAX_PAIRS pairs (about
- * 20 MiB), of which each device the library runs on holds one copy until the
- * process ends; its address is looked up once per context by paf_create.  The
- * call makes no hipMalloc, hipFree or other allocating call.  Every call on
- * one device shares that array: calls that overlap on the device (other
- * streams, other contexts of the device) race and their results are
- * undefined; calls on one stream, or ordered by the caller, do not.  Nothing
- * in the array needs clearing between calls.  n_pairs above the maximum
- * returns PAF_ERR_RANGE and launches nothing; PAF_ERR_DEVICE if the array's
- * address could not be looked up at paf_create. */
+/* paf_filter_magnet for callers that cannot allocate device memory: code under
+ * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
+ * arguments and outputs; the call makes no hipMalloc, hipFree or other
+ * allocating call.  n_pairs above PAF_MAGNET_NOALLOC_MAX_PAIRS returns
+ * PAF_ERR_RANGE and launches nothing (the limit of the static workspace that
+ * the call once had; it uses none now, so calls on several streams do not
+ * disturb each other). */
 #define PAF_MAGNET_NOALLOC_MAX_PAIRS 4194304
 paf_status paf_filter_magnet_noalloc(paf_ctx* ctx, const paf_batch* batch, const paf_out* out, void* stream);
 

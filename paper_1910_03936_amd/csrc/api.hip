@@ -306,6 +306,48 @@ paf_layout layout_for(paf_ctx* ctx, const FilterParams& p, int emax, bool queue_
     return plain_layout(emax);
 }
 
+// SneakySnake alone as paf_filter runs it: the flow engine or the compacting
+// engine, the latter as a full grid of chunks.  A forced layout sets its chunk
+// size and block shape, or turns it off.
+paf_status launch_snake(paf_ctx* ctx, FilterParams& p, int emax, const paf_layout* forced, hipStream_t stream) {
+    if (!forced && flow_serves(p)) {
+        PAF_HIP(launch_flow(p, emax, ctx->num_cus, stream), "filter launch");
+        return PAF_OK;
+    }
+    const paf_layout L = forced ? *forced : plain_layout(emax);
+    Engine eng = Engine::Snake;
+    LaunchShape sh;
+    sh.waves_per_block = p.wmax > 8 ? 2 : 4;
+    sh.lds_bytes = filter_lds_bytes(sh.waves_per_block, p.wmax);
+    uint64_t units = p.n_tiles;
+    const bool general = general_batch(p, eng, emax);
+    if (L.chunk_tiles > 0) {
+        paf_status st = PAF_OK;
+        eng = compacting_engine(L, emax, st);
+        if (st != PAF_OK) return st;
+        p.chunk = L.chunk_tiles;
+        p.span0 = std::max(1u, L.first_pass_windows);
+        p.span = std::max(1u, L.pass_windows);
+        sh.waves_per_block = L.waves_per_block;
+        sh.lds_bytes = chunk_lds_bytes(sh.waves_per_block, general, emax, p.chunk, L.lanes_per_pair);
+        if (sh.lds_bytes > 160 * 1024) return fail(PAF_ERR_RANGE, "layout needs more LDS than a CU has");
+        units = (p.n_tiles + p.chunk - 1) / p.chunk;
+    }
+    sh.blocks = (uint32_t)((units + sh.waves_per_block - 1) / sh.waves_per_block);
+    PAF_HIP(allow_lds(filter_kernel_ptr(eng, general, emax, p.filters), sh.lds_bytes), "hipFuncSetAttribute");
+    PAF_HIP(launch_filter(p, eng, general, emax, sh, stream), "filter launch");
+    return PAF_OK;
+}
+
+// MAGNET: SneakySnake into the caller's outputs, then MAGNET on its survivors.
+// (SneakySnake's own launch, whatever layout is forced.)
+paf_status run_magnet(paf_ctx* ctx, FilterParams& p, int emax, hipStream_t stream) {
+    paf_status st = launch_snake(ctx, p, emax, nullptr, stream);
+    if (st != PAF_OK || emax == 0) return st;
+    PAF_HIP(launch_magnet(p, emax, ctx->num_cus, stream), "MAGNET launch");
+    return PAF_OK;
+}
+
 void set_outputs(FilterParams& p, const paf_out* out) {
     for (int f = 0; f < 3; ++f) {
         p.acc[f] = ((p.filters >> f) & 1u) ? out->accept_bits[f] : nullptr;
@@ -345,11 +387,6 @@ paf_status paf_create(paf_ctx** out, int device) {
         delete c;
         return fail(PAF_ERR_DEVICE, "device initialisation failed");
     }
-    // The static workspace of paf_filter_magnet_noalloc: its address on this
-    // device (the device is current here).  A failed lookup only disables
-    // that entry point.
-    c->magnet_scratch_err = magnet_noalloc_address(&c->magnet_scratch);
-    if (c->magnet_scratch_err != hipSuccess) c->magnet_scratch = nullptr;
     *out = c;
     return PAF_OK;
 }
@@ -543,36 +580,16 @@ paf_status paf_filter(paf_ctx* ctx, const paf_batch* batch, uint32_t filters, co
         return paf_filter(ctx, batch, rest, out, stream);
     }
     set_outputs(p, out);
-    Engine eng = engine_for(filters);
-    const bool general = general_batch(p, eng, emax);
+    PAF_HIP(hipSetDevice(ctx->device), "hipSetDevice");
+    if (filters == PAF_SNEAKYSNAKE)
+        return launch_snake(ctx, p, emax, ctx->layout_forced ? &ctx->forced : nullptr, (hipStream_t)stream);
     LaunchShape sh;
     sh.waves_per_block = p.wmax > 8 ? 2 : 4;
     sh.lds_bytes = filter_lds_bytes(sh.waves_per_block, p.wmax);
-    uint64_t units = p.n_tiles;
-    // SneakySnake alone: the flow engine or the compacting engine, the latter
-    // as a full grid of chunks (a forced layout may set its chunk size and
-    // block shape, or turn it off).
-    if (eng == Engine::Snake && !ctx->layout_forced && flow_serves(p)) {
-        PAF_HIP(hipSetDevice(ctx->device), "hipSetDevice");
-        PAF_HIP(launch_flow(p, emax, ctx->num_cus, (hipStream_t)stream), "filter launch");
-        return PAF_OK;
-    }
-    const paf_layout PL = ctx->layout_forced ? ctx->forced : plain_layout(emax);
-    if (eng == Engine::Snake && PL.chunk_tiles > 0) {
-        eng = compacting_engine(PL, emax, st);
-        if (st != PAF_OK) return st;
-        p.chunk = PL.chunk_tiles;
-        p.span0 = std::max(1u, PL.first_pass_windows);
-        p.span = std::max(1u, PL.pass_windows);
-        sh.waves_per_block = PL.waves_per_block;
-        sh.lds_bytes = chunk_lds_bytes(sh.waves_per_block, general, emax, p.chunk, PL.lanes_per_pair);
-        if (sh.lds_bytes > 160 * 1024) return fail(PAF_ERR_RANGE, "layout needs more LDS than a CU has");
-        units = (p.n_tiles + p.chunk - 1) / p.chunk;
-    }
-    sh.blocks = (uint32_t)((units + sh.waves_per_block - 1) / sh.waves_per_block);
-    PAF_HIP(hipSetDevice(ctx->device), "hipSetDevice");
-    PAF_HIP(allow_lds(filter_kernel_ptr(eng, general, emax, p.filters), sh.lds_bytes), "hipFuncSetAttribute");
-    PAF_HIP(launch_filter(p, eng, general, emax, sh, (hipStream_t)stream), "filter launch");
+    sh.blocks = (uint32_t)((p.n_tiles + sh.waves_per_block - 1) / sh.waves_per_block);
+    const bool general = general_batch(p, Engine::Whole, emax);
+    PAF_HIP(allow_lds(filter_kernel_ptr(Engine::Whole, general, emax, p.filters), sh.lds_bytes), "hipFuncSetAttribute");
+    PAF_HIP(launch_filter(p, Engine::Whole, general, emax, sh, (hipStream_t)stream), "filter launch");
     return PAF_OK;
 }
 
@@ -620,13 +637,7 @@ paf_status paf_filter_magnet(paf_ctx* ctx, const paf_batch* batch, const paf_out
     if (emax < 0) return fail(PAF_ERR_RANGE, "max_E exceeds PAF_MAX_E");
     set_outputs(p, out);
     PAF_HIP(hipSetDevice(ctx->device), "hipSetDevice");
-    ScratchScope scope(ctx, (hipStream_t)stream);
-    if (scope.st != PAF_OK) return scope.st;
-    if ((st = ensure_bucket_ws(ctx, p.n_pairs)) != PAF_OK) return st;
-    PAF_HIP(launch_magnet(p, emax, ctx->ws_bucket, ctx->ws_counts, ctx->ws_perm, ctx->ws_hist, ctx->num_cus,
-                          (hipStream_t)stream),
-            "MAGNET launch");
-    return PAF_OK;
+    return run_magnet(ctx, p, emax, (hipStream_t)stream);
 }
 
 paf_status paf_filter_magnet_noalloc(paf_ctx* ctx, const paf_batch* batch, const paf_out* out, void* stream) {
@@ -639,13 +650,9 @@ paf_status paf_filter_magnet_noalloc(paf_ctx* ctx, const paf_batch* batch, const
         return fail(PAF_ERR_RANGE, "batch larger than the static workspace (PAF_MAGNET_NOALLOC_MAX_PAIRS pairs)");
     const int emax = emax_bucket((int)p.max_E);
     if (emax < 0) return fail(PAF_ERR_RANGE, "max_E exceeds PAF_MAX_E");
-    if (!ctx->magnet_scratch)
-        return hip_fail(ctx->magnet_scratch_err, "device address of the static MAGNET workspace");
     set_outputs(p, out);
     PAF_HIP(hipSetDevice(ctx->device), "hipSetDevice");
-    PAF_HIP(launch_magnet_noalloc(p, emax, ctx->magnet_scratch, ctx->num_cus, (hipStream_t)stream),
-            "MAGNET launch");
-    return PAF_OK;
+    return run_magnet(ctx, p, emax, (hipStream_t)stream);
 }
 
 paf_status paf_verify(paf_ctx* ctx, const paf_batch* batch, const uint32_t* select_bits, uint16_t* dist,
