@@ -140,6 +140,9 @@ paf_layout plain_layout(int emax) {
     return paf_layout{1u, 2u, 0u, 1u, 6u, 4u, 1u};
 }
 
+// Widest sub-mazes that are walked all at once.
+constexpr uint32_t kPartNarrowColumns = 16;
+
 // Launch shape of paf_filter_partitioned: paf_filter's, except at max_E 4 to
 // 6, where chunks of 6 tiles and one-window later passes measured 1.3-6.4%
 // faster on 10M pairs of 250 bp at E = 5 (t = 5, 10, 25, 50 and the fixed
@@ -609,11 +612,21 @@ paf_status paf_filter_partitioned(paf_ctx* ctx, const paf_batch* batch, uint32_t
     p.part_cap = y ? y : ~0u;
     const bool general = batch->len || batch->E || batch->word_offset;
     // The compacting engine, as a full grid of chunks (a forced layout that
-    // compacts sets the chunk size, block shape and pass widths).
-    const paf_layout PL = ctx->layout_forced && ctx->forced.chunk_tiles > 0 ? ctx->forced : part_layout(emax);
-    p.chunk = PL.chunk_tiles;
+    // compacts sets the chunk size, block shape and pass widths).  Chunks are
+    // cut smaller where the batch would not fill two waves per SIMD: 5k pairs
+    // 250 bp at E = 10 took 38 us in chunks of 6 tiles, 16 us in chunks of one.
+    const bool forced = ctx->layout_forced && ctx->forced.chunk_tiles > 0;
+    const paf_layout PL = forced ? ctx->forced : part_layout(emax);
+    const uint64_t fill = p.n_tiles / (8u * (uint64_t)ctx->num_cus);
+    p.chunk = forced ? PL.chunk_tiles
+                     : (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(PL.chunk_tiles, fill));
     p.span0 = std::max(1u, PL.first_pass_windows);
     p.span = std::max(1u, PL.pass_windows);
+    // Sub-mazes of a window all at once, or one probe at a time: 2M pairs at
+    // E = 10 take 115 / 232 us at t = 5, 125 / 190 at t = 10, 127 / 153 at
+    // t = 16, 156 / 167 at t = 25 and 163 / 160 at t = 50; 1M at E = 25 218 / 303
+    // at t = 10, 225 / 248 at t = 16 and 282 / 277 at t = 25.
+    const Engine eng = t <= kPartNarrowColumns ? Engine::ChunkPart : Engine::ChunkPartWide;
     LaunchShape sh;
     sh.waves_per_block = PL.waves_per_block;
     sh.lds_bytes = chunk_lds_bytes(sh.waves_per_block, general, emax, p.chunk, 1);
@@ -621,9 +634,9 @@ paf_status paf_filter_partitioned(paf_ctx* ctx, const paf_batch* batch, uint32_t
     const uint64_t units = (p.n_tiles + p.chunk - 1) / p.chunk;
     sh.blocks = (uint32_t)((units + sh.waves_per_block - 1) / sh.waves_per_block);
     PAF_HIP(hipSetDevice(ctx->device), "hipSetDevice");
-    PAF_HIP(allow_lds(filter_kernel_ptr(Engine::ChunkPart, general, emax, p.filters), sh.lds_bytes),
+    PAF_HIP(allow_lds(filter_kernel_ptr(eng, general, emax, p.filters), sh.lds_bytes),
             "hipFuncSetAttribute");
-    PAF_HIP(launch_filter(p, Engine::ChunkPart, general, emax, sh, (hipStream_t)stream), "filter launch");
+    PAF_HIP(launch_filter(p, eng, general, emax, sh, (hipStream_t)stream), "filter launch");
     return PAF_OK;
 }
 

@@ -133,6 +133,7 @@ __device__ void snake_tile(const FilterParams& P, uint64_t tile, int lane, uint6
 // mask of a snake that entered the window inside a pipe, and (general
 // layout) the pair's word offset.
 constexpr uint32_t kChunkMaxTiles = 16;
+constexpr int kPartNone = 0, kPartNarrow = 1, kPartWide = 2;
 
 struct ChunkEntry {
     uint32_t idx, c, e, m, E, ep;
@@ -172,6 +173,11 @@ __device__ __forceinline__ uint32_t or_xor3(uint32_t a, uint32_t t, uint32_t b) 
 }
 __device__ __forceinline__ uint32_t nor_xor3(uint32_t a, uint32_t t, uint32_t b) {
     return __builtin_amdgcn_bitop3_b32(a, t, b, 0x21);
+}
+
+// a & ~(s ^ h): the bits of a that s left out (h = 0) or has (h = 1).
+__device__ __forceinline__ uint32_t run_to_end(uint32_t a, uint32_t s, uint32_t h) {
+    return __builtin_amdgcn_bitop3_b32(a, s, h, 0x90);
 }
 
 template <int EMAX, int VAC, bool CONT, typename DT, int I = 0>
@@ -325,13 +331,20 @@ __device__ __forceinline__ WindowWords window_words_carried(const uint64_t* rd, 
 }
 
 // PART: the maze is cut into sub-mazes of P.part columns, each solved on its
-// own (Sec. 8.6; SneakySnake-t of Sec. 9.3.1).  A lane then also tracks pe,
-// the first column of the next sub-maze: a probe's run is cut at pe, reaching
-// pe costs nothing, and the snake leaves pe free to take any diagonal.  With
-// a cap y (P.part_cap), a sub-maze counts at most y obstacles: the hardware's
-// y replications each cross one, so after the y-th the snake moves on to pe
-// (a sub-maze then counts min(y, its fewest obstacles), the hardware's
-// min(y, w - sum x)).
+// own (Sec. 8.6; SneakySnake-t of Sec. 9.3.1): a probe's run ends at its
+// sub-maze's last column, reaching that costs nothing, and the snake enters the
+// next one free to take any diagonal.  With a cap y (P.part_cap), a sub-maze
+// counts at most y obstacles: the hardware's y replications each cross one, so
+// after the y-th the snake moves on to the next sub-maze (a sub-maze then
+// counts min(y, its fewest obstacles), the hardware's min(y, w - sum x)).
+//   kPartWide: one probe at a time; a lane tracks pe, the first column of the
+// next sub-maze, and cuts its probe's run there.
+//   kPartNarrow: as each sub-maze begins free, those of a window are walked all
+// at once, a probe taking one step in each: with 5 columns a window takes the
+// most steps that one of its 7 sub-mazes takes (2 or 3) where the other form
+// takes a probe for each sub-maze and each obstacle (about 13).  A step costs a
+// half more (the last columns are kept apart).  Both are bound by
+// instruction issue.
 //
 // Passes.  The first pass takes the chunk's pairs in order, 64 at a time:
 // up to EMAX 10 each lane loads the words of its pair's first two windows at
@@ -349,7 +362,7 @@ __device__ __forceinline__ WindowWords window_words_carried(const uint64_t* rd, 
 // and both lanes of a pair OR their runs after every probe (one DPP move), so
 // they walk the same snake; lane h = 0 writes the pair's outputs and list
 // entry, each lane its half of the dead-diagonal mask.
-template <int EMAX, bool GENERAL, bool PART, int LPP>
+template <int EMAX, bool GENERAL, int PART, int LPP>
 __device__ void chunk_snake(const FilterParams& P, uint32_t chunk, uint32_t K, int lane,
                             const ChunkLds<typename ChunkDead<EMAX, LPP>::T, GENERAL>& L) {
     constexpr int D = 2 * EMAX + 1;
@@ -377,6 +390,10 @@ __device__ void chunk_snake(const FilterParams& P, uint32_t chunk, uint32_t K, i
     const bool mask_E = GENERAL ? (P.E != nullptr || P.uniform_E < (uint32_t)EMAX)
                                 : (P.uniform_E < (uint32_t)EMAX);
     const bool keyed = P.order_key != nullptr && plain_out;
+    // Bits 0, P.part, 2 P.part, ... below 32.
+    uint32_t part_every = 1u;
+    if constexpr (PART == kPartNarrow)
+        for (uint32_t x = P.part; x < 32u; x += P.part) part_every |= 1u << x;
     uint32_t n_ent = 0;
     // Each pass walks windows [w, w + span) with the same lanes; the pairs
     // still undecided after it are regrouped for the next pass.
@@ -385,6 +402,8 @@ __device__ void chunk_snake(const FilterParams& P, uint32_t chunk, uint32_t K, i
         const bool first_pass = w == 0;
         const uint32_t n_in = first_pass ? n_here : n_ent;
         uint32_t n_out = 0;
+        // The first sub-maze that starts at or past the pass's first column.
+        const uint32_t part_next0 = PART == kPartNarrow ? (32u * w + P.part - 1u) / P.part * P.part : 0u;
         for (uint32_t g = 0; g < n_in; g += GS) {
             const uint32_t i = g + pl;
             bool act = i < n_in;
@@ -429,8 +448,9 @@ __device__ void chunk_snake(const FilterParams& P, uint32_t chunk, uint32_t K, i
             // A snake inside a pipe at a window's start is never at a
             // sub-maze's first column (reaching that column ends the pipe), so
             // pe follows from c alone.
-            uint32_t pe = PART ? (c / P.part + 1u) * P.part : 0u;
+            uint32_t pe = PART == kPartWide ? (c / P.part + 1u) * P.part : 0u;
             uint32_t ep = t.ep;
+            uint32_t part_next = part_next0;
             Carry cy = {0ull, 0ull};
             for (uint32_t wk = w; wk < w + span && wave_any(act); ++wk) {
                 WindowWords q;
@@ -477,8 +497,15 @@ __device__ void chunk_snake(const FilterParams& P, uint32_t chunk, uint32_t K, i
                 }
                 const uint32_t w0 = 32u * wk;
                 const bool live = act;
+                // Sub-mazes' first columns in the window and last ones.
+                const uint32_t first_in = part_next - w0;
+                const uint32_t part_starts = PART == kPartNarrow && first_in < 32u ? part_every << first_in : 0u;
+                const uint32_t part_ends =
+                    PART == kPartNarrow ? (part_starts >> 1) |
+                               (part_next + (uint32_t)__builtin_popcount(part_starts) * P.part == w0 + 32u ? 0x80000000u : 0u)
+                         : 0u;
                 uint32_t clear = 0, bs = 0;
-                if constexpr (PART) {
+                if constexpr (PART == kPartWide) {
                     // The snake state stays in plain integers (column c,
                     // edits e, the sub-maze's end pe and its edits ep), so the
                     // loop carries no lane masks beyond its own condition: the
@@ -517,6 +544,58 @@ __device__ void chunk_snake(const FilterParams& P, uint32_t chunk, uint32_t K, i
                         pe += nx ? P.part : 0u;
                         ep = nx ? 0u : ep;
                     }
+                } else if constexpr (PART == kPartNarrow) {
+                    // Every sub-maze that starts in the window, and the one
+                    // the window begins in, is walked at once: b holds the
+                    // probe's first column of each, `ends` each one's last
+                    // column (the pair's included).  A match word without its
+                    // `ends` cells stops a carry in the field it began in, at
+                    // its last column at the furthest, so
+                    // Z & ~((Z & ~ends) + b ^ ends) is each field's run, the
+                    // cell at its last column included when the carry got
+                    // there.  A field whose run reaches its last column (or
+                    // the window's end) is done; the others have one obstacle
+                    // each (ob) and go on after it.
+                    const uint32_t inpair = m >= w0 + 32u ? ~0u : (1u << ((m - w0) & 31u)) - 1u;
+                    const uint32_t last = m - 1u - w0;
+                    const uint32_t ends = part_ends | (last < 32u ? 1u << last : 0u);
+                    // The sub-maze the window begins in, and the one it ends in.
+                    const uint32_t part_in = part_starts & ~1u;
+                    const uint32_t lead = part_in ? (part_in & (0u - part_in)) - 1u : ~0u;
+                    const uint32_t trail = part_starts ? ~0u << (31 - __builtin_clz(part_starts)) : ~0u;
+                    if (part_starts & 1u) ep = 0;
+                    uint32_t b = act ? (part_starts | 1u) & inpair : 0u;
+                    if (ep >= P.part_cap) b &= ~lead;
+                    uint32_t obs = 0, starts = 0, reached = 0;
+                    const uint32_t left = E - e;
+                    uint32_t rounds = 0;
+                    while (b != 0u && (uint32_t)__builtin_popcount(obs) <= left) {
+                        uint32_t r0 = 0, r1 = 0;
+#pragma unroll
+                        for (int d = 0; d < D; d += 2) {
+                            r0 |= run_to_end(M[d], (M[d] & ~ends) + b, ends);
+                            if (d + 1 < D) r1 |= run_to_end(M[d + 1], (M[d + 1] & ~ends) + b, ends);
+                        }
+                        const uint32_t runs = r0 | r1;
+                        const uint32_t ob = ((runs & ~ends) + b) & ~(runs & ends);
+                        reached |= runs;
+                        starts |= b;
+                        obs |= ob;
+                        b = (ob & ~ends) << 1;
+                        ++rounds;
+                        if (rounds >= P.part_cap) b = 0u;
+                        if (ep + rounds >= P.part_cap) b &= ~lead;
+                    }
+                    if (live) {
+                        const uint32_t n_trail = (uint32_t)__builtin_popcount(obs & trail);
+                        e = min(e + (uint32_t)__builtin_popcount(obs), E + 1u);
+                        ep = part_starts ? n_trail : ep + n_trail;
+                        c = w0 + 32u;
+                        // The pipe of the window's last sub-maze goes on.
+                        clear = (reached & ~ends) >> 31;
+                        bs = 0x80000000u >> __builtin_clz(starts | 1u);
+                    }
+                    part_next += (uint32_t)__builtin_popcount(part_starts) * P.part;
                 } else {
                     // Every lane still undecided enters the window at its
                     // first column (it left the last one at its end), so the
@@ -694,9 +773,12 @@ __host__ __device__ constexpr size_t chunk_wave_bytes_t(uint32_t K) {
 // At EMAX 20 and 31 four waves with a few spilled registers measured faster
 // than three without (1.28 -> 1.22 and 2.42 -> 2.21 ms per 10M pairs of
 // 250 bp); at 25 they did not (1.64 either way), nor are they needed up to 15.
-template <int EMAX, bool GENERAL, bool PART, int LPP>
+// Narrow sub-mazes hold every match word twice, with and without the last
+// columns: four waves up to EMAX 10 (121 -> 115 us per 2M pairs at E = 10), the
+// registers they take above (266 -> 189 us per 500k pairs of 400 bp at E = 31).
+template <int EMAX, bool GENERAL, int PART, int LPP>
 __global__ void __launch_bounds__(512)
-__attribute__((amdgpu_waves_per_eu(LPP == 2 ? 4 : (EMAX <= 8 ? 5 : ((EMAX == 20 || EMAX == 31) ? 4 : 1)))))
+__attribute__((amdgpu_waves_per_eu(LPP == 2 ? 4 : (EMAX <= 8 ? 5 : (PART == kPartNarrow ? (EMAX <= 10 ? 4 : 1) : ((EMAX == 20 || EMAX == 31) ? 4 : 1))))))
 chunk_kernel(FilterParams P) {
     extern __shared__ uint64_t lds[];
     using DT = typename ChunkDead<EMAX, LPP>::T;
@@ -738,7 +820,7 @@ chunk_kernel(FilterParams P) {
     }
 }
 
-template <bool GENERAL, bool PART>
+template <bool GENERAL, int PART>
 const void* chunk_kernel_for(int emax) {
     switch (emax) {
 #define PAF_CASE(X) \
@@ -756,7 +838,7 @@ template <bool GENERAL>
 const void* chunk2_kernel_for(int emax) {
     switch (emax) {
 #define PAF_CASE(X) \
-    case X: return reinterpret_cast<const void*>(&chunk_kernel<X, GENERAL, false, 2>);
+    case X: return reinterpret_cast<const void*>(&chunk_kernel<X, GENERAL, kPartNone, 2>);
         PAF_CASE(10) PAF_CASE(12) PAF_CASE(15) PAF_CASE(20) PAF_CASE(25) PAF_CASE(31)
 #undef PAF_CASE
         default: return nullptr;
@@ -906,10 +988,12 @@ bool general_batch(const FilterParams& p, Engine eng, int emax) {
 }
 
 const void* filter_kernel_ptr(Engine eng, bool general, int emax, uint32_t filters) {
-    if (eng == Engine::Chunk) return general ? chunk_kernel_for<true, false>(emax) : chunk_kernel_for<false, false>(emax);
+    if (eng == Engine::Chunk) return general ? chunk_kernel_for<true, kPartNone>(emax) : chunk_kernel_for<false, kPartNone>(emax);
     if (eng == Engine::Chunk2) return general ? chunk2_kernel_for<true>(emax) : chunk2_kernel_for<false>(emax);
     if (eng == Engine::ChunkPart)
-        return general ? chunk_kernel_for<true, true>(emax) : chunk_kernel_for<false, true>(emax);
+        return general ? chunk_kernel_for<true, kPartNarrow>(emax) : chunk_kernel_for<false, kPartNarrow>(emax);
+    if (eng == Engine::ChunkPartWide)
+        return general ? chunk_kernel_for<true, kPartWide>(emax) : chunk_kernel_for<false, kPartWide>(emax);
     if (eng == Engine::Snake) return general ? snake_kernel_for<true>(emax) : snake_kernel_for<false>(emax);
     return whole_kernel_ptr(general, emax, filters);
 }

@@ -50,7 +50,7 @@ struct FilterParams {
 
 // Kernel selection.
 // Chunk2: the compacting engine with two lanes per pair (whole maze, max_E 9..31).
-enum class Engine { Snake, Whole, Chunk, ChunkPart, Chunk2 };
+enum class Engine { Snake, Whole, Chunk, ChunkPart, ChunkPartWide, Chunk2 };
 
 struct LaunchShape {
     uint32_t waves_per_block;
