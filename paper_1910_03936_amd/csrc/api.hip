@@ -677,7 +677,7 @@ paf_status paf_verify(paf_ctx* ctx, const paf_batch* batch, const uint32_t* sele
     const int emax = emax_bucket((int)p.max_E);
     if (emax < 0) return fail(PAF_ERR_RANGE, "max_E exceeds PAF_MAX_E");
     PAF_HIP(hipSetDevice(ctx->device), "hipSetDevice");
-    PAF_HIP(launch_verify(p, emax, select_bits, dist, (hipStream_t)stream),
+    PAF_HIP(launch_verify(p, emax, select_bits, dist, ctx->num_cus, (hipStream_t)stream),
             "verify launch");
     return PAF_OK;
 }

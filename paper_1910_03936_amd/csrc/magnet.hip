@@ -161,9 +161,10 @@ __global__ void __launch_bounds__(64) magnet_kernel(FilterParams P, uint32_t K) 
     const uint64_t slot0 = (uint64_t)blockIdx.x * K * 64;
     const uint32_t n_here = (uint32_t)min<uint64_t>((uint64_t)K * 64, P.n_pairs - slot0);
     uint32_t end = 0;
+    const uint32_t bits = chunk_bits(P.acc[0], slot0, n_here, lane);
     for (uint32_t g = 0; g < n_here; g += 64) {
         const uint32_t i = g + (uint32_t)lane;
-        const bool take = i < n_here && ((P.acc[0][(slot0 + i) >> 5] >> (i & 31u)) & 1u) != 0u;
+        const bool take = chunk_bit(bits, g >> 6, lane) && i < n_here;
         const uint64_t bal = __ballot(take);
         if (take) list[end + rank_in(bal)] = (uint16_t)i;
         end += (uint32_t)__builtin_popcountll(bal);

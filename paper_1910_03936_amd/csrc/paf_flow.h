@@ -118,5 +118,17 @@ __device__ __forceinline__ uint32_t rank_in(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// Words of a bit array for a wave's pairs slot0 .. slot0 + n - 1 (n <= 2048),
+// two per tile of 64: lane j loads word j, and the bits of a tile are read from
+// its lanes (a load per tile, each waited for, took 1 us apiece).
+__device__ __forceinline__ uint32_t chunk_bits(const uint32_t* bits, uint64_t slot0, uint32_t n, int lane) {
+    return 32u * (uint32_t)lane < n ? bits[(slot0 >> 5) + (uint32_t)lane] : 0u;
+}
+__device__ __forceinline__ bool chunk_bit(uint32_t words, uint32_t tile, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)words, (int)(2u * tile));
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)words, (int)(2u * tile + 1u));
+    return (((lane < 32 ? lo : hi) >> (lane & 31)) & 1u) != 0u;
+}
+
 }  // namespace
 }  // namespace paf

@@ -116,7 +116,8 @@ hipError_t launch_flow(FilterParams p, int emax, int num_cus, hipStream_t stream
 
 // verify.hip: banded edit distance of the selected pairs (sel: accept-bit
 // words, or NULL for every pair).
-hipError_t launch_verify(const FilterParams& p, int emax, const uint32_t* sel, uint16_t* dist, hipStream_t s);
+hipError_t launch_verify(const FilterParams& p, int emax, const uint32_t* sel, uint16_t* dist, int num_cus,
+                         hipStream_t s);
 
 // magnet.hip: MAGNET's counts and accept bits of the pairs whose bit is set in
 // p.acc[0] (p.cnt[0] and p.acc[0] hold SneakySnake's, which are right for the

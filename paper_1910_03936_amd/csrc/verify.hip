@@ -17,194 +17,213 @@
 // found 32 bases at a time from the planar two-bit words: an XOR per code
 // plane, an OR, and a count of trailing zeros.
 //
+// Every lane walks its own rounds and diagonals: a step is 32 bases of one run,
+// after which the lane goes on with the run, the next diagonal or the next
+// round.  F and the pair's words are in LDS columns of the lane's own, where
+// any lane can be at any diagonal (in registers they force the lanes of a wave
+// through the same diagonal together, as long as the longest run among them:
+// a third of the lanes did work then).  A lane whose pair is decided takes the
+// next one of the wave's list.
+//
+// Bound: the latency of a step's two LDS trips and its instruction issue,
+// about 40 steps of 60 vector instructions a pair.  Measured, 250 bp unless
+// said, against a lane per pair with F in registers: 4M pairs at E = 10 (333k
+// survivors of SneakySnake) 130 -> 72 us, 1k pairs 44 -> 18, 500k E = 25 472 ->
+// 122, 300k 500 bp E = 31 850 -> 187, 500k related pairs E = 15 773 -> 115, 4M
+// 100 bp E = 3 19.0 -> 15.6.
+//
 // A selection (optional, e.g. the accept bits of a filter) names the pairs
 // to verify; the others get E + 1.
-#include "paf_tile.h"
+#include <algorithm>
+
+#include "paf_flow.h"
 
 namespace paf {
 
 namespace {
 
-constexpr int kNeg = -(1 << 20);
+constexpr int kUnreached = -(1 << 14);
 
-// 32 bases of one staged sequence from base position p on (planes lo, hi).
-__device__ __forceinline__ void bases32(const uint64_t* rows, int lane, uint32_t p, uint32_t W, uint32_t& lo,
-                                        uint32_t& hi) {
-    const uint32_t k = p >> 5, sh = p & 31u;
-    const uint64_t w0 = rows[k * kLdsRow + lane];
-    const uint64_t w1 = k + 1 < W ? rows[(k + 1) * kLdsRow + lane] : 0ull;
-    lo = funnel((uint32_t)w1, (uint32_t)w0, sh);
-    hi = funnel((uint32_t)(w1 >> 32), (uint32_t)(w0 >> 32), sh);
+// A wave owns K tiles of 64 consecutive pairs and lists the ones selected (bit
+// p of `sel`, or all when sel is NULL).
+constexpr uint32_t kVerifyTiles = 32;
+// Idle lanes that are worth the trip to memory for their next pairs' words (8
+// and 16 measured the same, 32 7% slower).
+constexpr int kRefill = 16;
+// Waves per SIMD that a launch aims at: one / two / three / four take 81 / 71 / 72 / 72 us
+// for 4M pairs at E = 10 and 20 / 18.6 / 15.6 / 14.9 us for 4M of 100 bp at
+// E = 3; fewer where the LDS holds fewer.
+constexpr uint32_t kVerifyWaves = 3;
+
+// Rows of F: diagonals -emax - 1 .. emax + 1.
+__host__ __device__ constexpr uint32_t reach_rows(uint32_t emax) { return 2 * emax + 3; }
+
+// Rows of words: two past the last one may be read.
+__host__ __device__ constexpr uint32_t word_rows(uint32_t wmax) { return wmax + 2; }
+
+// LDS of a wave, in the 1280-byte units it is allocated in.
+constexpr size_t verify_lds_bytes(uint32_t wmax, uint32_t emax, uint32_t tiles) {
+    const size_t b = (size_t)64 * (2 * word_rows(wmax) * 8 + reach_rows(emax) * 2 + tiles * 2);
+    return (b + 1279) / 1280 * 1280;
 }
 
-// Furthest column reached on diagonal d from column x (x <= end): the run of
-// matches ref[c] == read[c + d] for c = x, x+1, ... stops at the first
-// mismatch or at end = min(m, m - d).
-__device__ __forceinline__ int slide(const uint64_t* rdL, const uint64_t* rfL, int lane, int x, int d,
-                                     int end, uint32_t W) {
-    int c = x;
-    while (c < end) {
-        uint32_t alo, ahi, blo, bhi;
-        bases32(rfL, lane, (uint32_t)c, W, alo, ahi);
-        bases32(rdL, lane, (uint32_t)(c + d), W, blo, bhi);
-        const uint32_t mism = (alo ^ blo) | (ahi ^ bhi);
-        if (mism != 0u) {
-            c += (int)__builtin_ctz(mism);
-            break;
-        }
-        c += 32;
-    }
-    return min(c, end);
+// 32 bases of a lane's sequence from base position p on (planes lo, hi); past
+// the pair's end they are any.
+__device__ __forceinline__ void bases32(const uint64_t* col, uint32_t p, uint32_t& lo, uint32_t& hi) {
+    const uint64_t* w = col + ((p & ~31u) << 1);
+    lo = funnel((uint32_t)w[64], (uint32_t)w[0], p);
+    hi = funnel((uint32_t)(w[64] >> 32), (uint32_t)(w[0] >> 32), p);
 }
 
-template <int EMAX>
-__device__ uint32_t band_distance(const uint64_t* rdL, const uint64_t* rfL, int lane, bool act, int m, int E,
-                                  uint32_t W) {
-    constexpr int D = 2 * EMAX + 1;
-    int F[D];
-#pragma unroll
-    for (int i = 0; i < D; ++i) F[i] = kNeg;
-    uint32_t dist = (uint32_t)E + 1u;
-    if (act) {
-        F[EMAX] = slide(rdL, rfL, lane, 0, 0, m, W);
-        if (F[EMAX] >= m) dist = 0;
-        if (F[EMAX] >= m || E == 0) act = false;
-    }
-    // Diagonals beyond the pair's threshold or length stay unreachable.  A
-    // path on diagonal d after k edits needs |d| more to end on diagonal 0,
-    // so round k only extends the diagonals with k + |d| <= E: the others
-    // cannot lie on an alignment within E edits (and the rounds after k
-    // only read diagonals that round k kept).
-    const int lim = min(E, m);
-    for (int k = 1; wave_any(act); ++k) {
-        if (act) {
-            int left = kNeg;   // F_{k-1}[d-1]
-            const int reach = min(k, min(lim, E - k));
-#pragma unroll
-            for (int i = 0; i < D; ++i) {
-                const int d = i - EMAX;
-                const int old = F[i];
-                const int ad = d < 0 ? -d : d;
-                if (ad <= reach) {
-                    int x = old + 1;
-                    if (i + 1 < D) x = max(x, F[i + 1] + 1);
-                    x = max(x, left);
-                    const int end = d > 0 ? m - d : m;
-                    x = min(x, end);
-                    F[i] = slide(rdL, rfL, lane, x, d, end, W);
-                }
-                left = old;
-            }
-            if (F[EMAX] >= m) {
-                dist = (uint32_t)k;
-                act = false;
-            } else if (k >= E) {
-                act = false;
-            }
-        }
-    }
-    return dist;
-}
-
-// Verification in chunks: a wave owns K tiles of 64 consecutive pairs
-// (K <= kVerifyTiles), lists the ones selected (bit p of `sel`, or all when sel is NULL) in
-// its LDS, writes E + 1 for the others, and then takes the list 64 entries at
-// a time: their words are staged in the wave's LDS rows, word-major, and
-// every lane runs its pair.  Filtered batches keep a few pairs in a hundred,
-// so the list turns a chunk's scattered survivors into full waves, with no
-// pass over the whole batch and no global atomics.  With every pair selected
-// a chunk is one tile (the groups are full anyway, and more waves run).
-constexpr uint32_t kVerifyTiles = 16;
-
-template <int EMAX>
-__global__ void __launch_bounds__(256) verify_kernel(FilterParams P, const uint32_t* sel, uint16_t* dist,
-                                                     uint32_t K) {
+__global__ void __launch_bounds__(64) verify_kernel(FilterParams P, const uint32_t* sel, uint16_t* dist, uint32_t K,
+                                                    uint32_t emax) {
     extern __shared__ uint64_t lds[];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const size_t rows = (size_t)2 * P.wmax * kLdsRow;
-    uint64_t* rdL = lds + (size_t)wave * (rows + kVerifyTiles * 64 / 4);
-    uint64_t* rfL = rdL + (size_t)P.wmax * kLdsRow;
-    uint16_t* list = reinterpret_cast<uint16_t*>(rdL + rows);
-    const uint64_t chunk = (uint64_t)blockIdx.x * (blockDim.x >> 6) + wave;
-    const uint64_t slot0 = chunk * K * 64;
-    if (slot0 >= P.n_pairs) return;
+    const int lane = threadIdx.x;
+    const uint32_t words = word_rows(P.wmax) * 64;
+    uint64_t* const rd = lds + lane;
+    uint64_t* const rf = rd + words;
+    int16_t* const F = reinterpret_cast<int16_t*>(lds + 2 * words) + (emax + 1) * 64 + lane;   // F[64 d]: diagonal d
+    uint16_t* const list = reinterpret_cast<uint16_t*>(lds + 2 * words) + reach_rows(emax) * 64;
+    const uint64_t slot0 = (uint64_t)blockIdx.x * K * 64;
     const uint32_t n_here = (uint32_t)min<uint64_t>((uint64_t)K * 64, P.n_pairs - slot0);
     uint32_t n_sel = 0;
-    for (uint32_t g = 0; g < n_here; g += 64) {
-        const uint32_t i = g + (uint32_t)lane;
-        const uint64_t p = slot0 + i;
-        bool take = false;
-        if (i < n_here) {
-            const uint32_t m = P.len ? P.len[p] : P.uniform_len;
-            const uint32_t E = P.E ? P.E[p] : P.uniform_E;
-            if (m < 1 || m > P.max_len || E > P.max_E) {
-                atomicOr(P.err, 1u);
-                dist[p] = 0;
-            } else if (sel == nullptr || ((sel[p >> 5] >> (p & 31u)) & 1u) != 0u) {
-                take = true;
-            } else {
-                dist[p] = (uint16_t)(E + 1u);
-            }
+    const uint32_t bits = sel ? chunk_bits(sel, slot0, n_here, lane) : ~0u;
+    constexpr uint32_t AHEAD = 4;   // tiles whose lengths and thresholds are loaded together
+    for (uint32_t g0 = 0; g0 < n_here; g0 += 64 * AHEAD) {
+        uint32_t ms[AHEAD], Es[AHEAD];
+#pragma unroll
+        for (uint32_t j = 0; j < AHEAD; ++j) {
+            const uint64_t p = slot0 + min(g0 + 64 * j + (uint32_t)lane, n_here - 1u);
+            ms[j] = P.len ? P.len[p] : P.uniform_len;
+            Es[j] = P.E ? P.E[p] : P.uniform_E;
         }
-        const uint64_t bal = __ballot(take);
-        const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
-                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-        if (take) list[n_sel + below] = (uint16_t)i;
-        n_sel += (uint32_t)__builtin_popcountll(bal);
+#pragma unroll
+        for (uint32_t j = 0; j < AHEAD; ++j) {
+            const uint32_t g = g0 + 64 * j;
+            if (g >= n_here) break;
+            const uint32_t i = g + (uint32_t)lane;
+            bool take = chunk_bit(bits, g >> 6, lane) && i < n_here;
+            if (i < n_here) {
+                if (ms[j] < 1 || ms[j] > P.max_len || Es[j] > P.max_E) {
+                    atomicOr(P.err, 1u);
+                    take = false;
+                    dist[slot0 + i] = 0;
+                } else if (!take) {
+                    dist[slot0 + i] = (uint16_t)(Es[j] + 1u);
+                }
+            }
+            const uint64_t bal = __ballot(take);
+            if (take) list[n_sel + rank_in(bal)] = (uint16_t)i;
+            n_sel += (uint32_t)__builtin_popcountll(bal);
+        }
     }
     wave_lds_sync();
-    for (uint32_t h = 0; h < n_sel; h += 64) {
-        const uint32_t j = h + (uint32_t)lane;
-        PairSlot s;
-        s.valid = j < n_sel;
-        s.in_batch = s.valid;
-        s.slot = s.id = s.valid ? slot0 + list[j] : 0;
-        s.m = s.valid ? (P.len ? P.len[s.id] : P.uniform_len) : 0u;
-        s.E = s.valid ? (P.E ? P.E[s.id] : P.uniform_E) : 0u;
-        s.W = (s.m + 31) >> 5;
-        const uint64_t off = !s.valid ? 0
-                             : P.word_offset ? P.word_offset[s.id]
-                                             : s.id * (uint64_t)P.stride_words;
-        stage_tile<true>(P, 0, lane, s, off, rdL, rfL);
-        const uint32_t dd = band_distance<EMAX>(rdL, rfL, lane, s.valid, (int)s.m, (int)s.E, s.W);
-        if (s.valid) dist[s.id] = (uint16_t)dd;
-        wave_lds_sync();
-    }
-}
 
-const void* verify_kernel_for(int emax) {
-    switch (emax) {
-#define PAF_CASE(X) \
-    case X: return reinterpret_cast<const void*>(&verify_kernel<X>);
-        PAF_CASE(0) PAF_CASE(1) PAF_CASE(2) PAF_CASE(3) PAF_CASE(4) PAF_CASE(5) PAF_CASE(6)
-        PAF_CASE(7) PAF_CASE(8) PAF_CASE(10) PAF_CASE(12) PAF_CASE(15) PAF_CASE(20) PAF_CASE(25)
-        PAF_CASE(31)
-#undef PAF_CASE
-        default: return nullptr;
+    // The lane's pair, its round k (over diagonals -reach .. reach, reach =
+    // min(k, cap, E - k)), the diagonal d being walked at column c, which ends
+    // at column `end`, and F_{k-1}[d].  An idle lane has m = 0 and stays at
+    // column 0 of diagonal 0.
+    uint64_t id = 0;
+    int m = 0, E = 0, cap = 0, k = 0, d = 0, c = 0, end = 0, here = 0;
+    uint32_t next = 0;
+    uint64_t idle = ~0ull;
+    for (;;) {
+        if (next < n_sel) {
+            const uint32_t at = next + rank_in(idle);
+            if (m == 0 && at < n_sel) {
+                id = slot0 + list[at];
+                m = (int)(P.len ? P.len[id] : P.uniform_len);
+                E = (int)(P.E ? P.E[id] : P.uniform_E);
+                const uint64_t off = P.word_offset ? P.word_offset[id] : id * (uint64_t)P.stride_words;
+                const uint64_t* gr = P.reads + off;
+                const uint64_t* gf = P.refs + off;
+                const int W = (m + 31) >> 5;
+                int w = 0;
+                for (; w + 4 <= W; w += 4) {
+                    uint64_t a[4], b[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        a[j] = gr[w + j];
+                        b[j] = gf[w + j];
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        rd[(w + j) * 64] = a[j];
+                        rf[(w + j) * 64] = b[j];
+                    }
+                }
+                for (; w < W; ++w) {
+                    rd[w * 64] = gr[w];
+                    rf[w * 64] = gf[w];
+                }
+                for (int j = -E - 1; j <= E + 1; ++j) F[j * 64] = (int16_t)kUnreached;
+                cap = min(E, m);
+                k = d = c = 0;
+                end = m;
+                here = kUnreached;
+            }
+            next = min(n_sel, next + (uint32_t)__builtin_popcountll(idle));
+        } else if (idle == ~0ull) {
+            break;
+        }
+        const int most = next < n_sel ? kRefill : 64;
+        do {
+            uint32_t alo, ahi, blo, bhi;
+            bases32(rf, (uint32_t)c, alo, ahi);
+            bases32(rd, (uint32_t)(c + d), blo, bhi);
+            const uint32_t mism = or_xor(ahi, alo ^ blo, bhi);
+            const int run = (int)min((uint32_t)(__builtin_ffs((int)mism) - 1), 32u);
+            c = min(c + run, end);
+            if (m != 0 && (mism != 0u || c >= end)) {
+                F[d * 64] = (int16_t)c;
+                const bool whole = d == 0 && c >= m;
+                const int found = whole ? k : E + 1;
+                // Diagonals beyond the pair's threshold or length stay unreachable.
+                // A path on diagonal d after k edits needs |d| more to end on
+                // diagonal 0, so round k only extends the diagonals with
+                // k + |d| <= E: the others cannot lie on an alignment within E
+                // edits (and the rounds after k only read diagonals that round k
+                // kept).
+                const int reach0 = min(k, min(cap, E - k));
+                const bool wrap = d == reach0;
+                k += wrap ? 1 : 0;
+                const int reach = min(k, min(cap, E - k));
+                const bool over = whole || k > E;
+                d = over ? 0 : wrap ? -reach : d + 1;
+                const int16_t* const f = F + d * 64;
+                const int before = wrap ? f[-64] : here, after = f[64];
+                here = f[0];
+                end = min(m, m - d);
+                c = min(max(max(here, after) + 1, before), end);
+                if (over) {
+                    dist[id] = (uint16_t)found;
+                    m = c = end = 0;
+                }
+            }
+            idle = __ballot(m == 0);
+        } while (__builtin_popcountll(idle) < most);
     }
 }
 
 }  // namespace
 
-hipError_t launch_verify(const FilterParams& p, int emax, const uint32_t* sel, uint16_t* dist, hipStream_t s) {
-    const void* k = verify_kernel_for(emax);
-    if (!k) return hipErrorInvalidValue;
-    // Four waves (four chunks) per block.
-    const uint32_t waves = 4;
-    uint32_t K = sel ? kVerifyTiles : 1u;
-    const size_t lds = (size_t)waves * ((size_t)2 * p.wmax * kLdsRow * sizeof(uint64_t) + kVerifyTiles * 64 * 2);
-    const uint64_t chunks = (p.n_pairs + K * 64 - 1) / (K * 64);
-    const uint32_t blocks = (uint32_t)((chunks + waves - 1) / waves);
-    FilterParams arg = p;
-    const uint32_t* sl = sel;
-    uint16_t* d = dist;
-    void* args[] = {&arg, &sl, &d, &K};
-    if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
+hipError_t launch_verify(const FilterParams& p, int emax, const uint32_t* sel, uint16_t* dist, int num_cus,
+                         hipStream_t s) {
+    // All waves run at once where the tiles allow it: a second turn of few
+    // waves costs as much as a full one (4M pairs at E = 10: 96 us with 2500
+    // waves, of which the LDS holds 2304 at once; 72 with 2233).
+    uint32_t K = 1;
+    for (;;) {
+        const uint64_t fit = 160 * 1024 / verify_lds_bytes(p.wmax, (uint32_t)emax, K);
+        const uint64_t want = (uint64_t)num_cus * std::min<uint64_t>(4 * kVerifyWaves, fit);
+        const uint32_t need = (uint32_t)std::min<uint64_t>(kVerifyTiles, (p.n_tiles + want - 1) / want);
+        if (need <= K) break;
+        K = need;
     }
-    return hipLaunchKernel(k, dim3(blocks), dim3(64 * waves), args, lds, s);
+    const uint64_t chunks = (p.n_tiles + K - 1) / K;
+    const size_t lds = verify_lds_bytes(p.wmax, (uint32_t)emax, K);
+    verify_kernel<<<dim3((uint32_t)chunks), dim3(64), lds, s>>>(p, sel, dist, K, (uint32_t)emax);
+    return hipGetLastError();
 }
 
 }  // namespace paf
