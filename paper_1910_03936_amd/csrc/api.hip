@@ -143,6 +143,17 @@ paf_layout plain_layout(int emax) {
 // Widest sub-mazes that are walked all at once.
 constexpr uint32_t kPartNarrowColumns = 16;
 
+// Tiles per chunk of a batch too small to give every SIMD four chunks of
+// `most` tiles.  250 bp at E = 10 (SneakySnake alone), chunks of 1 / 2 / 4 / 6
+// tiles: 100k pairs 21 / 25 / 34 / 49 us, 500k 55 / 40 / 44 / 61, 1M 98 / 71 / 68 /
+// 84, 2M 181 / 129 / 120 / 122.  (3 tiles take 51 at 500k and 72 at 1M.)
+uint32_t fitted_chunk(const paf_ctx* ctx, const FilterParams& p, uint32_t most) {
+    const uint64_t simds4 = 16u * (uint64_t)ctx->num_cus;
+    uint64_t k = (p.n_tiles + simds4 - 1) / simds4;
+    if (k == 3) k = 4;
+    return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(most, k));
+}
+
 // Launch shape of paf_filter_partitioned: paf_filter's, except at max_E 4 to
 // 6, where chunks of 6 tiles and one-window later passes measured 1.3-6.4%
 // faster on 10M pairs of 250 bp at E = 5 (t = 5, 10, 25, 50 and the fixed
@@ -306,7 +317,9 @@ paf_layout layout_for(paf_ctx* ctx, const FilterParams& p, int emax, bool queue_
     auto it = ctx->tuned.find(std::make_tuple((int)p.wmax, emax, p.filters));
     if (it != ctx->tuned.end()) return it->second;
     if (queue_default) return default_layout();
-    return plain_layout(emax);
+    paf_layout L = plain_layout(emax);
+    L.chunk_tiles = fitted_chunk(ctx, p, L.chunk_tiles);
+    return L;
 }
 
 // SneakySnake alone as paf_filter runs it: the flow engine or the compacting
@@ -612,14 +625,10 @@ paf_status paf_filter_partitioned(paf_ctx* ctx, const paf_batch* batch, uint32_t
     p.part_cap = y ? y : ~0u;
     const bool general = batch->len || batch->E || batch->word_offset;
     // The compacting engine, as a full grid of chunks (a forced layout that
-    // compacts sets the chunk size, block shape and pass widths).  Chunks are
-    // cut smaller where the batch would not fill two waves per SIMD: 5k pairs
-    // 250 bp at E = 10 took 38 us in chunks of 6 tiles, 16 us in chunks of one.
+    // compacts sets the chunk size, block shape and pass widths).
     const bool forced = ctx->layout_forced && ctx->forced.chunk_tiles > 0;
     const paf_layout PL = forced ? ctx->forced : part_layout(emax);
-    const uint64_t fill = p.n_tiles / (8u * (uint64_t)ctx->num_cus);
-    p.chunk = forced ? PL.chunk_tiles
-                     : (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(PL.chunk_tiles, fill));
+    p.chunk = forced ? PL.chunk_tiles : fitted_chunk(ctx, p, PL.chunk_tiles);
     p.span0 = std::max(1u, PL.first_pass_windows);
     p.span = std::max(1u, PL.pass_windows);
     // Sub-mazes of a window all at once, or one probe at a time: 2M pairs at
