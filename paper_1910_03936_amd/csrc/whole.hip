@@ -17,7 +17,7 @@ namespace {
 // registers included) take about 2.4 cycles a wave and funnel shifts, shifts
 // left, field extracts and compares about 4.3: the diagonals are worked on with
 // as few of the latter as the definitions allow.  2M pairs of 250 bp at E = 10:
-// GateKeeper 148 -> 112 us (opening once a window instead of amending every
+// GateKeeper 148 -> 104 us (opening once a window instead of amending every
 // diagonal), Shouji 400 -> 264 us (eight ranks instead of a ones count, and the
 // store by table look-up instead of ten instructions a column), the two
 // together 543 -> 282 us (one set of raw words instead of a map each, which
@@ -140,23 +140,13 @@ __device__ __forceinline__ uint32_t shouji_store(const uint16_t* table, const Sh
     return total >> 8;
 }
 
-// Raw mismatch words of a window; diagonals beyond the pair's threshold are
-// all ones (the ones that can lie beyond it, see over_E).
+// Diagonals beyond the pair's threshold are all ones (the ones that can lie
+// beyond it, see over_E).
 template <int EMAX, bool GENERAL>
 __host__ __device__ constexpr bool may_exceed(int ad) {
     return GENERAL ? ad > 0 : ad > emax_below(EMAX) + 1;
 }
 __device__ __forceinline__ uint32_t over_E(uint32_t E, int ad) { return (uint32_t)((int32_t)(E - (uint32_t)ad) >> 31); }
-
-template <int EMAX, bool GENERAL, int I = 0>
-__device__ __forceinline__ void build_raw(const WindowWords& q, uint32_t E, uint32_t* R) {
-    if constexpr (I < 2 * EMAX + 1) {
-        constexpr int d = I - EMAX, ad = d < 0 ? -d : d;
-        R[I] = diag_raw<d>(q);
-        if constexpr (may_exceed<EMAX, GENERAL>(ad)) R[I] |= over_E(E, ad);
-        build_raw<EMAX, GENERAL, I + 1>(q, E, R);
-    }
-}
 
 // Vacant and past-end cells of a window (none on the diagonals beyond the
 // threshold, whose words are ones for every stage).
@@ -173,6 +163,49 @@ __device__ __forceinline__ uint32_t diag_blank(const Vacancy& v, uint32_t E) {
     if constexpr (d < 0) x |= funnel(v.vc, v.vp, 32 + d);
     if constexpr (MASK) x &= ~over_E(E, d < 0 ? -d : d);
     return x;
+}
+
+// A window's words as they are kept: raw where two stages share them, else
+// with the vacant and past-end cells folded in for the stage that reads them
+// (kFree: GateKeeper, kBlocked: Shouji), so that no window's are worked out
+// twice: 2M uneven pairs 180 -> 140 us for GateKeeper, 364 -> 321 for Shouji.
+// (blank_words is a pass of its own over the windows that have such cells: as
+// two branches of one pass the words of both were live.)
+constexpr int kRaw = 0, kFree = 1, kBlocked = 2;
+template <int EMAX, bool GENERAL, bool BLOCK, int I = 0>
+__device__ __forceinline__ void build_raw(const WindowWords& q, uint32_t E, uint32_t* R) {
+    if constexpr (I < 2 * EMAX + 1) {
+        constexpr int d = I - EMAX, ad = d < 0 ? -d : d;
+        R[I] = diag_raw<d>(q);
+        if constexpr (BLOCK && may_exceed<EMAX, GENERAL>(ad)) R[I] |= over_E(E, ad);
+        build_raw<EMAX, GENERAL, BLOCK, I + 1>(q, E, R);
+    }
+}
+template <int EMAX, int KEEP, int I = 0>
+__device__ __forceinline__ void blank_words(const Vacancy& v, uint32_t* R) {
+    if constexpr (I < 2 * EMAX + 1) {
+        const uint32_t x = diag_blank<I - EMAX, false>(v, 0u);
+        R[I] = KEEP == kFree ? R[I] & ~x : R[I] | x;
+        blank_words<EMAX, KEEP, I + 1>(v, R);
+    }
+}
+template <int EMAX, bool GENERAL, int I = 0>
+__device__ __forceinline__ void block_over_E(uint32_t E, uint32_t* R) {
+    if constexpr (I < 2 * EMAX + 1) {
+        constexpr int d = I - EMAX, ad = d < 0 ? -d : d;
+        if constexpr (may_exceed<EMAX, GENERAL>(ad)) R[I] |= over_E(E, ad);
+        block_over_E<EMAX, GENERAL, I + 1>(E, R);
+    }
+}
+template <int EMAX, bool GENERAL, int KEEP>
+__device__ __forceinline__ void build_words(const WindowWords& q, const Vacancy& v, bool blanks, uint32_t E, uint32_t* R) {
+    build_raw<EMAX, GENERAL, KEEP == kRaw>(q, E, R);
+    if constexpr (KEEP == kRaw) return;
+    if (blanks) blank_words<EMAX, KEEP>(v, R);
+    // Many diagonals' masks are worked out again each window, not held (they
+    // would take the registers of a wave per SIMD).
+    if constexpr (GENERAL && EMAX > 15) asm volatile("" : "+v"(E));
+    block_over_E<EMAX, GENERAL>(E, R);
 }
 
 // GateKeeper (Ch. 5, Sec. 5.2.2): the amendment turns streaks of one or two
@@ -216,14 +249,15 @@ __device__ __forceinline__ void blocked_words(const uint32_t* R, const Vacancy& 
 
 // The starts of runs of three zeros in the two columns before the first: their
 // runs reach column 0 (all of it free on some diagonal, or columns 0 and 1).
-template <int EMAX, bool GENERAL, int I = 0>
+template <int EMAX, bool GENERAL, int KEEP, int I = 0>
 __device__ __forceinline__ void left_starts(const uint32_t* R, const Vacancy& v, uint32_t E, uint32_t& one, uint32_t& two) {
     if constexpr (I < 2 * EMAX + 1) {
         constexpr int d = I - EMAX, ad = d < 0 ? -d : d;
-        const uint32_t g = R[I] & ~diag_blank<d, may_exceed<EMAX, GENERAL>(ad)>(v, E);
+        uint32_t g = R[I];
+        if constexpr (KEEP == kRaw) g &= ~diag_blank<d, may_exceed<EMAX, GENERAL>(ad)>(v, E);
         one &= g;
         two &= g | (g >> 1);
-        left_starts<EMAX, GENERAL, I + 1>(R, v, E, one, two);
+        left_starts<EMAX, GENERAL, KEEP, I + 1>(R, v, E, one, two);
     }
 }
 
@@ -239,6 +273,11 @@ __device__ void whole_tile(const FilterParams& P, uint64_t tile, int lane, uint6
     stage_tile<GENERAL>(P, tile, lane, ps, off, rdL, rfL);
 
     constexpr bool RT = FS == 0;
+    // (Shouji's blocked words pay where some lane's pair ends in most windows, and
+    // where registers are short: 2M uniform pairs at E = 10 264 us raw, 273
+    // blocked; 500k at E = 25 149 and 133.)
+    constexpr int KEEP = FS == PAF_GATEKEEPER ? kFree
+                         : FS == PAF_SHOUJI && (GENERAL || EMAX > 15) ? kBlocked : kRaw;
     constexpr bool GKS = RT || (FS & PAF_GATEKEEPER), SHS = RT || (FS & PAF_SHOUJI), SSS = RT;
     const bool doSS = RT && (P.filters & PAF_SNEAKYSNAKE) != 0;
     const bool doGK = RT ? (P.filters & PAF_GATEKEEPER) != 0 : GKS;
@@ -254,10 +293,10 @@ __device__ void whole_tile(const FilterParams& P, uint64_t tile, int lane, uint6
     uint32_t Ra[D], Rb[D];
     {
         const WindowWords q = window_words(rdL, rfL, lane, 0, P.wmax, (int)m);
-        build_raw<EMAX, GENERAL>(q, E, Ra);
+        build_words<EMAX, GENERAL, KEEP>(q, vacancy_of(0, (int)m), true, E, Ra);
         if (GKS && doGK) {
             uint32_t one = ~0u, two = ~0u;
-            left_starts<EMAX, GENERAL>(Ra, vacancy_of(0, (int)m), E, one, two);
+            left_starts<EMAX, GENERAL, KEEP>(Ra, vacancy_of(0, (int)m), E, one, two);
             prev_starts = (~one & 1u) << 30 | (~two & 1u) << 31;
         }
     }
@@ -266,11 +305,12 @@ __device__ void whole_tile(const FilterParams& P, uint64_t tile, int lane, uint6
     // their results are not counted.
     auto window = [&](uint32_t w, const uint32_t (&Rc)[D], uint32_t (&Rn)[D]) {
         const bool have = ps.valid && w < ps.W;
-        build_raw<EMAX, GENERAL>(window_words(rdL, rfL, lane, (int)w + 1, P.wmax, (int)m), E, Rn);
         const uint32_t past = have ? vacant_word((int)w, (int)m) : ~0u;   // columns >= m
         const Vacancy vc = vacancy_of((int)w, (int)m), vn = vacancy_of((int)w + 1, (int)m);
         // Cells of this window or the next one are vacant only near the ends.
-        const bool inner = !wave_any(have && (w == 0u || 32u * (w + 2u) + (uint32_t)EMAX > m));
+        const bool inner_n = !wave_any(have && 32u * (w + 2u) + (uint32_t)EMAX > m);
+        const bool inner = KEEP != kRaw || (inner_n && w != 0u);
+        build_words<EMAX, GENERAL, KEEP>(window_words(rdL, rfL, lane, (int)w + 1, P.wmax, (int)m), vn, !inner_n, E, Rn);
         if constexpr (SSS)
             if (doSS && have && z.act) {
                 uint32_t M[D];
@@ -282,7 +322,7 @@ __device__ void whole_tile(const FilterParams& P, uint64_t tile, int lane, uint6
         auto diagonals = [&](auto gk, auto sh) {
             constexpr bool G = decltype(gk)::value, S = decltype(sh)::value;
             if (inner) whole_diagonals<EMAX, GENERAL, true, G, S>(Rc, Rn, vc, vn, E, starts, bs);
-            else whole_diagonals<EMAX, GENERAL, false, G, S>(Rc, Rn, vc, vn, E, starts, bs);
+            else if constexpr (KEEP == kRaw) whole_diagonals<EMAX, GENERAL, false, G, S>(Rc, Rn, vc, vn, E, starts, bs);
         };
         using yes = std::true_type;
         using no = std::false_type;
