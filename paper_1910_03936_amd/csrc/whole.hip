@@ -305,12 +305,14 @@ __device__ void whole_tile(const FilterParams& P, uint64_t tile, int lane, uint6
     // their results are not counted.
     auto window = [&](uint32_t w, const uint32_t (&Rc)[D], uint32_t (&Rn)[D]) {
         const bool have = ps.valid && w < ps.W;
+        const WindowWords qn = window_words(rdL, rfL, lane, (int)w + 1, P.wmax, (int)m);
+        if constexpr (KEEP == kRaw) build_raw<EMAX, GENERAL, true>(qn, E, Rn);
         const uint32_t past = have ? vacant_word((int)w, (int)m) : ~0u;   // columns >= m
         const Vacancy vc = vacancy_of((int)w, (int)m), vn = vacancy_of((int)w + 1, (int)m);
         // Cells of this window or the next one are vacant only near the ends.
-        const bool inner_n = !wave_any(have && 32u * (w + 2u) + (uint32_t)EMAX > m);
-        const bool inner = KEEP != kRaw || (inner_n && w != 0u);
-        build_words<EMAX, GENERAL, KEEP>(window_words(rdL, rfL, lane, (int)w + 1, P.wmax, (int)m), vn, !inner_n, E, Rn);
+        const bool inner_n = !wave_any(have && ((KEEP == kRaw && w == 0u) || 32u * (w + 2u) + (uint32_t)EMAX > m));
+        const bool inner = KEEP != kRaw || inner_n;
+        if constexpr (KEEP != kRaw) build_words<EMAX, GENERAL, KEEP>(qn, vn, !inner_n, E, Rn);
         if constexpr (SSS)
             if (doSS && have && z.act) {
                 uint32_t M[D];
