@@ -227,7 +227,7 @@ paf_status paf_filter_magnet_noalloc(paf_ctx* ctx, const paf_batch* batch, const
  * verifying every pair, since SneakySnake never rejects a pair within E
  * edits.  dist [device]: n_pairs uint16, at the original pair index.  Work
  * grows with each pair's distance (by diagonal transition, E+1 rounds at
- * most); each wave lists the selected pairs of up to 2048 consecutive ones and
+ * most); each wave lists the selected pairs of up to 4096 consecutive ones and
  * its lanes take them as they finish, so only the selected pairs cost time.
  * Needs no workspace. */
 paf_status paf_verify(paf_ctx* ctx, const paf_batch* batch, const uint32_t* select_bits, uint16_t* dist,

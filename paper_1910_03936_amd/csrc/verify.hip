@@ -45,7 +45,10 @@ namespace {
 constexpr int kUnreached = -(1 << 14);
 
 // A wave owns K tiles of 64 consecutive pairs and lists the ones selected (bit
-// p of `sel`, or all when sel is NULL).
+// p of `sel`).
+// Up to 32, or 64 where that avoids a second turn of long chains (max_E 20 and
+// up): 4M pairs at E = 25 627 us in one turn, 877 in two; at E = 10 10M pairs
+// 0.17 ms in three turns, 0.21 in two of longer chunks.
 constexpr uint32_t kVerifyTiles = 32;
 // Idle lanes that are worth the trip to memory for their next pairs' words (8
 // and 16 measured the same, 32 7% slower).
@@ -87,7 +90,8 @@ __global__ void __launch_bounds__(64) verify_kernel(FilterParams P, const uint32
     const uint64_t slot0 = (uint64_t)blockIdx.x * K * 64;
     const uint32_t n_here = (uint32_t)min<uint64_t>((uint64_t)K * 64, P.n_pairs - slot0);
     uint32_t n_sel = 0;
-    const uint32_t bits = sel ? chunk_bits(sel, slot0, n_here, lane) : ~0u;
+    const uint32_t bits0 = chunk_bits(sel, slot0, min(n_here, 2048u), lane);
+    const uint32_t bits1 = n_here > 2048u ? chunk_bits(sel, slot0 + 2048u, n_here - 2048u, lane) : 0u;
     constexpr uint32_t AHEAD = 4;   // tiles whose lengths and thresholds are loaded together
     for (uint32_t g0 = 0; g0 < n_here; g0 += 64 * AHEAD) {
         uint32_t ms[AHEAD], Es[AHEAD];
@@ -102,7 +106,7 @@ __global__ void __launch_bounds__(64) verify_kernel(FilterParams P, const uint32
             const uint32_t g = g0 + 64 * j;
             if (g >= n_here) break;
             const uint32_t i = g + (uint32_t)lane;
-            bool take = chunk_bit(bits, g >> 6, lane) && i < n_here;
+            bool take = chunk_bit(g < 2048u ? bits0 : bits1, (g >> 6) & 31u, lane) && i < n_here;
             if (i < n_here) {
                 if (ms[j] < 1 || ms[j] > P.max_len || Es[j] > P.max_E) {
                     atomicOr(P.err, 1u);
@@ -205,18 +209,161 @@ __global__ void __launch_bounds__(64) verify_kernel(FilterParams P, const uint32
     }
 }
 
+// 32 bases of one staged sequence from base position p on (planes lo, hi).
+__device__ __forceinline__ void staged32(const uint64_t* rows, int lane, uint32_t p, uint32_t W, uint32_t& lo,
+                                        uint32_t& hi) {
+    const uint32_t k = p >> 5, sh = p & 31u;
+    const uint64_t w0 = rows[k * kLdsRow + lane];
+    const uint64_t w1 = k + 1 < W ? rows[(k + 1) * kLdsRow + lane] : 0ull;
+    lo = funnel((uint32_t)w1, (uint32_t)w0, sh);
+    hi = funnel((uint32_t)(w1 >> 32), (uint32_t)(w0 >> 32), sh);
+}
+
+// Furthest column reached on diagonal d from column x (x <= end): the run of
+// matches ref[c] == read[c + d] for c = x, x+1, ... stops at the first
+// mismatch or at end = min(m, m - d).
+__device__ __forceinline__ int slide(const uint64_t* rdL, const uint64_t* rfL, int lane, int x, int d,
+                                     int end, uint32_t W) {
+    int c = x;
+    while (c < end) {
+        uint32_t alo, ahi, blo, bhi;
+        staged32(rfL, lane, (uint32_t)c, W, alo, ahi);
+        staged32(rdL, lane, (uint32_t)(c + d), W, blo, bhi);
+        const uint32_t mism = (alo ^ blo) | (ahi ^ bhi);
+        if (mism != 0u) {
+            c += (int)__builtin_ctz(mism);
+            break;
+        }
+        c += 32;
+    }
+    return min(c, end);
+}
+
+template <int EMAX>
+__device__ uint32_t band_distance(const uint64_t* rdL, const uint64_t* rfL, int lane, bool act, int m, int E,
+                                  uint32_t W) {
+    constexpr int D = 2 * EMAX + 1;
+    int F[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) F[i] = kUnreached;
+    uint32_t dist = (uint32_t)E + 1u;
+    if (act) {
+        F[EMAX] = slide(rdL, rfL, lane, 0, 0, m, W);
+        if (F[EMAX] >= m) dist = 0;
+        if (F[EMAX] >= m || E == 0) act = false;
+    }
+    // Diagonals beyond the pair's threshold or length stay unreachable.  A
+    // path on diagonal d after k edits needs |d| more to end on diagonal 0,
+    // so round k only extends the diagonals with k + |d| <= E: the others
+    // cannot lie on an alignment within E edits (and the rounds after k
+    // only read diagonals that round k kept).
+    const int lim = min(E, m);
+    for (int k = 1; wave_any(act); ++k) {
+        if (act) {
+            int left = kUnreached;   // F_{k-1}[d-1]
+            const int reach = min(k, min(lim, E - k));
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                const int d = i - EMAX;
+                const int old = F[i];
+                const int ad = d < 0 ? -d : d;
+                if (ad <= reach) {
+                    int x = old + 1;
+                    if (i + 1 < D) x = max(x, F[i + 1] + 1);
+                    x = max(x, left);
+                    const int end = d > 0 ? m - d : m;
+                    x = min(x, end);
+                    F[i] = slide(rdL, rfL, lane, x, d, end, W);
+                }
+                left = old;
+            }
+            if (F[EMAX] >= m) {
+                dist = (uint32_t)k;
+                act = false;
+            } else if (k >= E) {
+                act = false;
+            }
+        }
+    }
+    return dist;
+}
+
+// Every pair of a batch, a tile of 64 per wave, its words staged in the wave's
+// LDS rows, the lanes walking rounds and diagonals together.  Most pairs then
+// need all E + 1 rounds, so that hardly a lane waits for another, and a step
+// takes half the instructions.
+template <int EMAX>
+__global__ void __launch_bounds__(256) verify_step_kernel(FilterParams P, uint16_t* dist) {
+    extern __shared__ uint64_t lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    uint64_t* rdL = lds + (size_t)wave * 2 * P.wmax * kLdsRow;
+    uint64_t* rfL = rdL + (size_t)P.wmax * kLdsRow;
+    const uint64_t slot0 = ((uint64_t)blockIdx.x * (blockDim.x >> 6) + wave) * 64;
+    if (slot0 >= P.n_pairs) return;
+    PairSlot s;
+    s.in_batch = slot0 + lane < P.n_pairs;
+    s.slot = s.id = s.in_batch ? slot0 + lane : 0;
+    s.m = s.in_batch ? (P.len ? P.len[s.id] : P.uniform_len) : 0u;
+    s.E = s.in_batch ? (P.E ? P.E[s.id] : P.uniform_E) : 0u;
+    s.valid = s.in_batch && s.m >= 1 && s.m <= P.max_len && s.E <= P.max_E;
+    if (s.in_batch && !s.valid) {
+        atomicOr(P.err, 1u);
+        dist[s.id] = 0;
+    }
+    if (!s.valid) s.m = s.E = 0;
+    s.W = (s.m + 31) >> 5;
+    const uint64_t off = !s.valid ? 0
+                         : P.word_offset ? P.word_offset[s.id]
+                                         : s.id * (uint64_t)P.stride_words;
+    stage_tile<true>(P, 0, lane, s, off, rdL, rfL);
+    const uint32_t dd = band_distance<EMAX>(rdL, rfL, lane, s.valid, (int)s.m, (int)s.E, s.W);
+    if (s.valid) dist[s.id] = (uint16_t)dd;
+}
+
+const void* verify_step_kernel_for(int emax) {
+    switch (emax) {
+#define PAF_CASE(X) \
+    case X: return reinterpret_cast<const void*>(&verify_step_kernel<X>);
+        PAF_CASE(0) PAF_CASE(1) PAF_CASE(2) PAF_CASE(3) PAF_CASE(4) PAF_CASE(5) PAF_CASE(6)
+        PAF_CASE(7) PAF_CASE(8) PAF_CASE(10) PAF_CASE(12) PAF_CASE(15) PAF_CASE(20) PAF_CASE(25)
+        PAF_CASE(31)
+#undef PAF_CASE
+        default: return nullptr;
+    }
+}
+
+hipError_t launch_steps(const FilterParams& p, int emax, uint16_t* dist, hipStream_t s) {
+    const void* k = verify_step_kernel_for(emax);
+    if (!k) return hipErrorInvalidValue;
+    const uint32_t waves = 4;
+    const size_t lds = (size_t)waves * 2 * p.wmax * kLdsRow * sizeof(uint64_t);
+    if (lds > 65536) {
+        hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    FilterParams arg = p;
+    void* args[] = {&arg, &dist};
+    return hipLaunchKernel(k, dim3((p.n_tiles + waves - 1) / waves), dim3(64 * waves), args, lds, s);
+}
+
 }  // namespace
 
 hipError_t launch_verify(const FilterParams& p, int emax, const uint32_t* sel, uint16_t* dist, int num_cus,
                          hipStream_t s) {
-    // All waves run at once where the tiles allow it: a second turn of few
-    // waves costs as much as a full one (4M pairs at E = 10: 96 us with 2500
-    // waves, of which the LDS holds 2304 at once; 72 with 2233).
+    // Every pair of 10M at E = 5 / 10 / 25: 0.45 / 0.97 / 4.94 ms in step, 0.66 /
+    // 1.77 / 9.05 lane by lane.
+    if (sel == nullptr) return launch_steps(p, emax, dist, s);
+    // All waves run at once where the tiles allow it, else in full turns: a
+    // turn of few waves costs as much as a full one (4M pairs at E = 10: 96 us
+    // with 2500 waves, of which the LDS holds 2304 at once; 72 with 2233).
     uint32_t K = 1;
     for (;;) {
         const uint64_t fit = 160 * 1024 / verify_lds_bytes(p.wmax, (uint32_t)emax, K);
         const uint64_t want = (uint64_t)num_cus * std::min<uint64_t>(4 * kVerifyWaves, fit);
-        const uint32_t need = (uint32_t)std::min<uint64_t>(kVerifyTiles, (p.n_tiles + want - 1) / want);
+        const uint64_t most = want * (emax >= 20 && p.n_tiles <= want * 2 * kVerifyTiles ? 2 * kVerifyTiles : kVerifyTiles);
+        const uint64_t turns = std::max<uint64_t>(1, (p.n_tiles + most - 1) / most);
+        const uint32_t need = (uint32_t)((p.n_tiles + want * turns - 1) / (want * turns));
         if (need <= K) break;
         K = need;
     }

@@ -57,3 +57,22 @@ def test_violation_inside_a_list(gpu_ctx):
     good[70_001] = 0
     assert np.array_equal(got, good)
     gpu_ctx.check()
+
+
+def test_lists_of_more_than_32_tiles(gpu_ctx):
+    # One small batch over and over (its rows repeated on the device), so many
+    # pairs that a wave lists more than 2048 of them; the repeats' distances
+    # are the small batch's.
+    base = 64 * 512
+    p = pairgen.generate(pairgen.FIXED_250BP.with_E(25), 11, base)
+    b = to_device(p, gpu_ctx, per_pair=False, offsets=False)
+    times = 120
+    n = base * times
+    big = paf.Batch(reads=b.reads.repeat(times, 1) if b.reads.dim() > 1 else b.reads.repeat(times),
+                    refs=b.refs.repeat(times, 1) if b.refs.dim() > 1 else b.refs.repeat(times),
+                    n_pairs=n, stride_words=b.stride_words, uniform_len=b.uniform_len, uniform_E=b.uniform_E,
+                    max_len=b.max_len, max_E=b.max_E)
+    want = oracle.banded_batch(p.reads, p.refs, p.len, p.E).astype(np.int64)
+    got = _dist(gpu_ctx.verify(big, gpu_ctx.filter(big, SS)[SS][0])).reshape(times, base)
+    assert np.array_equal(got, np.broadcast_to(want, got.shape))
+    gpu_ctx.check()
