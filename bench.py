@@ -219,8 +219,9 @@ def record_traffic(args):
     fs = gib / (max(v["FETCH_SIZE"] for _, v in _counter_csv(os.path.join(d, "cfetch")).values()) * 1024)
     ws = gib / (max(v["WRITE_SIZE"] for _, v in _counter_csv(os.path.join(d, "cwrite")).values()) * 1024)
     # The levels kernel's second template argument picks its form (two tiles
-    # of words in flight on uniform batches); either form counts.
-    kernels = {"snake_chunk": (f"chunk_kernel<{args.E}, false, false, 1>(",),
+    # of words in flight on uniform batches); either form counts.  (The
+    # filter's third argument, the partition's form, was a flag.)
+    kernels = {"snake_chunk": (f"chunk_kernel<{args.E}, false, 0, 1>(", f"chunk_kernel<{args.E}, false, false, 1>("),
                "key_levels": (f"key_kernel<{args.E}>(", f"key_kernel<{args.E}, true>(", f"key_kernel<{args.E}, false>(")}
     rec = {}
 
