@@ -916,6 +916,11 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t* row, int k) { return *rei
 
 constexpr int kMlpThreads = 512;   // eight waves: one 16-wide strip of hidden units each
 
+// Rows of one inference launch: kMlpThreads threads per kTile rows, and a launch
+// holds fewer than 2^32 threads (one of 2^32 returned no error and left rows out).
+constexpr uint64_t kForwardRows = 1u << 28;
+static_assert(kForwardRows % kTile == 0 && kForwardRows / kTile * kMlpThreads < 1ull << 32, "threads of a launch");
+
 template <bool TRAIN>
 __global__ void __launch_bounds__(kMlpThreads) mlp_kernel(TrainArgs a) {
     __shared__ __attribute__((aligned(16))) typename std::conditional<TRAIN, TrainLds, ForwardLds>::type L;
@@ -1438,9 +1443,8 @@ paf_status paf_mlp_forward(paf_ctx* ctx, const float* features, uint64_t n, floa
     if (scope.st != PAF_OK) return scope.st;
     hipStream_t s = (hipStream_t)stream;
     const MlpDev& m = ctx->mlp;
-    const uint64_t chunk = 1u << 30;
-    for (uint64_t a = 0; a < n; a += chunk) {
-        const uint32_t k = (uint32_t)std::min<uint64_t>(chunk, n - a);
+    for (uint64_t a = 0; a < n; a += kForwardRows) {
+        const uint32_t k = (uint32_t)std::min<uint64_t>(kForwardRows, n - a);
         const TrainArgs t{features + a * kFeat, nullptr, k, kTile, m.w1b, m.w2b, m.w2tb, m.w3r, m.master, out + a, nullptr};
         hipLaunchKernelGGL(mlp_kernel<false>, dim3((k + kTile - 1) / kTile), dim3(kMlpThreads), 0, s, t);
         PAF_HIP(hipGetLastError(), "forward");
