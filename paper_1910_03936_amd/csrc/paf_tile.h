@@ -246,8 +246,31 @@ __device__ __forceinline__ void snake_window(Snake& z, const uint32_t* M, uint32
 // from the persistent work queue until it runs dry.  The next take is issued
 // before the current tiles are processed, so the queue's round trip overlaps
 // the work; every wave leaves after its first empty take.
-template <typename F>
+// ONE_CALL: `run` is called in one place for both (a large tile function that
+// is called in two places is not inlined, and the call saves registers to
+// scratch: see whole_kernel).
+template <bool ONE_CALL = false, typename F>
 __device__ __forceinline__ void for_each_tile(const FilterParams& P, int lane, int wave, F&& run) {
+    if constexpr (ONE_CALL) {
+        const bool queued = P.queue != nullptr;
+        uint32_t t0 = blockIdx.x * (blockDim.x >> 6) + (uint32_t)wave;
+        if (queued) {
+            if (lane == 0) t0 = atomicAdd(P.queue, P.grab);
+            t0 = __shfl(t0, 0);
+        }
+        while (t0 < P.n_tiles) {
+            uint32_t nx = 0;
+            if (queued && lane == 0) nx = atomicAdd(P.queue, P.grab);
+            const uint32_t t1 = queued ? min(P.n_tiles, t0 + P.grab) : t0 + 1u;
+            for (uint32_t t = t0; t < t1; ++t) {
+                run(t);
+                wave_lds_sync();
+            }
+            if (!queued) break;
+            t0 = __shfl(nx, 0);
+        }
+        return;
+    }
     if (P.queue == nullptr) {
         const uint64_t tile = (uint64_t)blockIdx.x * (blockDim.x >> 6) + wave;
         if (tile < P.n_tiles) run(tile);

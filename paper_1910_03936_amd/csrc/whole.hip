@@ -278,8 +278,8 @@ __device__ void whole_tile(const FilterParams& P, uint64_t tile, int lane, uint6
     // blocked; 500k at E = 25 149 and 133.)
     constexpr int KEEP = FS == PAF_GATEKEEPER ? kFree
                          : FS == PAF_SHOUJI && (GENERAL || EMAX > 15) ? kBlocked : kRaw;
-    constexpr bool GKS = RT || (FS & PAF_GATEKEEPER), SHS = RT || (FS & PAF_SHOUJI), SSS = RT;
-    const bool doSS = RT && (P.filters & PAF_SNEAKYSNAKE) != 0;
+    constexpr bool GKS = RT || (FS & PAF_GATEKEEPER), SHS = RT || (FS & PAF_SHOUJI), SSS = RT || (FS & PAF_SNEAKYSNAKE);
+    const bool doSS = RT ? (P.filters & PAF_SNEAKYSNAKE) != 0 : SSS;
     const bool doGK = RT ? (P.filters & PAF_GATEKEEPER) != 0 : GKS;
     const bool doSH = RT ? (P.filters & PAF_SHOUJI) != 0 : SHS;
     const uint32_t m = ps.m, E = ps.E;
@@ -366,9 +366,16 @@ __device__ void whole_tile(const FilterParams& P, uint64_t tile, int lane, uint6
     // (two windows a turn, so that no window's words are copied on)
     for (uint32_t w = 0;; w += 2) {
         if (!wave_any(ps.valid && w < ps.W)) break;
-        window(w, Ra, Rb);
-        if (!wave_any(ps.valid && w + 1 < ps.W)) break;
-        window(w + 1, Rb, Ra);
+        if constexpr (RT) {
+            // (as a function it takes the words through scratch)
+            [[clang::always_inline]] window(w, Ra, Rb);
+            if (!wave_any(ps.valid && w + 1 < ps.W)) break;
+            [[clang::always_inline]] window(w + 1, Rb, Ra);
+        } else {
+            window(w, Ra, Rb);
+            if (!wave_any(ps.valid && w + 1 < ps.W)) break;
+            window(w + 1, Rb, Ra);
+        }
     }
 
     const bool gk_acc = gk_ham <= E || gk_cnt <= E;
@@ -399,7 +406,7 @@ __global__ void __launch_bounds__(256) whole_kernel(FilterParams P) {
     __shared__ typename std::conditional<TABLE, ShoujiTable, uint4>::type table;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    if constexpr (TABLE) {
+    if (TABLE && (FS != 0 || (P.filters & PAF_SHOUJI) != 0)) {
         for (uint32_t i = threadIdx.x; i < sizeof(ShoujiTable) / 16; i += blockDim.x)
             reinterpret_cast<uint4*>(&table)[i] = reinterpret_cast<const uint4*>(&kShoujiTable)[i];
         __syncthreads();
@@ -407,7 +414,13 @@ __global__ void __launch_bounds__(256) whole_kernel(FilterParams P) {
     uint64_t* rdL = lds + (size_t)wave * 2 * P.wmax * kLdsRow;
     uint64_t* rfL = rdL + (size_t)P.wmax * kLdsRow;
     const uint16_t* tab = reinterpret_cast<const uint16_t*>(&table);
-    for_each_tile(P, lane, wave, [&](uint64_t tile) { whole_tile<EMAX, GENERAL, FS>(P, tile, lane, rdL, rfL, tab); });
+    // The masks read at run time in one place where pairs have lengths and
+    // thresholds of their own: 100k at E = 15, SneakySnake and Shouji, 216 us in
+    // two, 185 in one; 1M of 400 bp at E = 31, all three, 4945 and 2146.  (The
+    // others are the faster form inlined twice: GateKeeper and Shouji on 1M pairs
+    // at E = 10 149 us, 158 in one place.)
+    for_each_tile<FS == 0 && GENERAL>(P, lane, wave,
+                                      [&](uint64_t tile) { whole_tile<EMAX, GENERAL, FS>(P, tile, lane, rdL, rfL, tab); });
 }
 
 template <bool GENERAL, int FS>
@@ -425,8 +438,10 @@ const void* whole_for(int emax) {
 
 }  // namespace
 
-// GateKeeper, Shouji and the two together get kernels of their own; the masks
-// with SneakySnake run on the kernel that reads the mask at run time.
+// GateKeeper, Shouji, the two together and SneakySnake with GateKeeper get
+// kernels of their own (the last: 1M pairs at E = 5 in a given order 133 us on the
+// kernel below, 122 on its own); SneakySnake with Shouji and all three run on
+// the kernel that reads the mask at run time.
 const void* whole_kernel_ptr(bool general, int emax, uint32_t filters) {
     switch (filters) {
         case PAF_GATEKEEPER: return general ? whole_for<true, PAF_GATEKEEPER>(emax) : whole_for<false, PAF_GATEKEEPER>(emax);
@@ -434,6 +449,9 @@ const void* whole_kernel_ptr(bool general, int emax, uint32_t filters) {
         case PAF_GATEKEEPER | PAF_SHOUJI:
             return general ? whole_for<true, PAF_GATEKEEPER | PAF_SHOUJI>(emax)
                            : whole_for<false, PAF_GATEKEEPER | PAF_SHOUJI>(emax);
+        case PAF_SNEAKYSNAKE | PAF_GATEKEEPER:
+            return general ? whole_for<true, PAF_SNEAKYSNAKE | PAF_GATEKEEPER>(emax)
+                           : whole_for<false, PAF_SNEAKYSNAKE | PAF_GATEKEEPER>(emax);
         default: return general ? whole_for<true, 0>(emax) : whole_for<false, 0>(emax);
     }
 }
