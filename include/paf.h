@@ -201,7 +201,8 @@ paf_status paf_filter_partitioned(paf_ctx* ctx, const paf_batch* batch, uint32_t
  * SneakySnake, MAGNET may reject a pair within E edits (Sec. 9.3.3).  Writes
  * out->accept_bits[0] and out->count[0] (the other slots are ignored).  Runs
  * SneakySnake into them first and MAGNET on the pairs it accepts (it accepts
- * every pair that MAGNET accepts); needs no workspace. */
+ * every pair that MAGNET accepts; with max_E 0 it only compares the words);
+ * needs no workspace. */
 paf_status paf_filter_magnet(paf_ctx* ctx, const paf_batch* batch, const paf_out* out, void* stream);
 
 /* paf_filter_magnet for callers that cannot allocate device memory: code under

@@ -358,8 +358,12 @@ paf_status launch_snake(paf_ctx* ctx, FilterParams& p, int emax, const paf_layou
 // MAGNET: SneakySnake into the caller's outputs, then MAGNET on its survivors.
 // (SneakySnake's own launch, whatever layout is forced.)
 paf_status run_magnet(paf_ctx* ctx, FilterParams& p, int emax, hipStream_t stream) {
+    if (emax == 0) {
+        PAF_HIP(launch_magnet_exact(p, stream), "MAGNET launch");
+        return PAF_OK;
+    }
     paf_status st = launch_snake(ctx, p, emax, nullptr, stream);
-    if (st != PAF_OK || emax == 0) return st;
+    if (st != PAF_OK) return st;
     PAF_HIP(launch_magnet(p, emax, ctx->num_cus, stream), "MAGNET launch");
     return PAF_OK;
 }

@@ -12,8 +12,7 @@
 // them, so when they cover m - E columns or more, the columns they leave out
 // are at most E obstacles of a path through the maze; SneakySnake, which finds
 // the fewest obstacles, then accepts the pair.  A pair it rejects is rejected
-// here too, with the same count E + 1 (and with E = 0 it decides every pair).
-// So the call runs SneakySnake into the caller's outputs and the kernel below
+// here too, with the same count E + 1.  So the call runs SneakySnake into the caller's outputs and the kernel below
 // on the pairs whose accept bit is set: 8% of the 250 bp workload at E = 10,
 // where a test of each diagonal for a run of m / (E + 1) free cells (Sec. 7.2's
 // first test) took longer than SneakySnake does and left 33%.
@@ -36,8 +35,8 @@
 // lane's window at its own column, into LDS; then the extractions.  A pair with
 // more intervals than a lane's part of the LDS holds, or with two runs that
 // overlap by more than kBack columns at a long run's end (repeats), is done
-// by the wave together, a lane per diagonal, by extracting from the diagonals'
-// runs themselves.
+// by a group of lanes together, a lane per diagonal, by extracting from the
+// diagonals' runs themselves.
 //
 // Bound: the serial chain of a group (about 25 windows of its longest pair, each
 // a trip to memory and 2E + 1 diagonals of shifts and compares, then E + 1
@@ -111,42 +110,108 @@ __device__ __forceinline__ uint32_t ival(uint32_t s, uint32_t len) { return (len
 __device__ __forceinline__ uint32_t ival_len(uint32_t v) { return v >> 10; }
 __device__ __forceinline__ uint32_t ival_start(uint32_t v) { return 1023u - (v & 1023u); }
 
-// One pair by the whole wave: lane i searches diagonal i - E.  gone: the
-// columns that left the search (one word per lane 0..15).
-__device__ __noinline__ uint32_t magnet_pair_by_wave(const uint64_t* rd, const uint64_t* rf, uint32_t m, uint32_t E, int lane) {
-    const int W = (int)((m + 31u) >> 5), d = lane - (int)E;
-    const uint32_t sh = (uint32_t)d & 31u;
-    uint32_t gone = vacant_word(lane, (int)m), covered = 0, it = 0;
-    for (;;) {
-        uint32_t best = 0, carry = 0;
-        for (int k = 0; k < W; ++k) {
-            const uint32_t out = (uint32_t)__shfl((int)gone, k);
-            const WindowWords q = window_words_direct(rd, rf, k, W, (int)m);
-            const bool pos = d >= 0;
-            const uint32_t lo = funnel(pos ? q.nlo : q.clo, pos ? q.clo : q.plo, sh);
-            const uint32_t hi = funnel(pos ? q.nhi : q.chi, pos ? q.chi : q.phi, sh);
-            const uint32_t v = funnel(pos ? q.vn : q.vc, pos ? q.vc : q.vp, sh);
-            const uint32_t x = lane <= 2 * (int)E ? ~((lo ^ q.flo) | (hi ^ q.fhi) | v | out) : 0u;
-            const uint32_t t = x == ~0u ? 32u : (uint32_t)__builtin_ctz(~x);
-            best = max(best, ival(32u * k - carry, carry + t));
-            if (x != ~0u) {
-                uint32_t L, s;
-                word_longest(x, L, s);
-                best = max(best, ival(32u * k + s, L));
-            }
-            carry = x == ~0u ? carry + 32u : (uint32_t)__builtin_clz(~x);
-        }
-        best = max(best, ival(32u * W - carry, carry));
+// Largest value of each group of G lanes (16, 32 or 64), in all of its lanes.
+template <int G>
+__device__ __forceinline__ uint32_t group_max(uint32_t v) {
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xF, 0xF, false));   // row_ror:1
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xF, 0xF, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xF, 0xF, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, false));
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) best = max(best, (uint32_t)__shfl_xor((int)best, o));
-        const uint32_t L = ival_len(best), s = ival_start(best);
-        if (L == 0u) break;
-        ++it;
-        covered += L;
-        gone |= cols_mask(lane, s > 0u ? s - 1u : 0u, min(s + L + 1u, m));
-        if (it > E) break;
+    for (int o = 16; o < G; o <<= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o));
+    return v;
+}
+
+// 64 / G pairs at once, lane i of a group searching diagonal i - E of the
+// group's pair (m = 0: none), whose words of free cells it keeps in its LDS
+// column `x` (`pair`: the pair's read and reference words, in turn).  A pass
+// over the words that any diagonal still has free cells in clears the columns
+// that left the search and finds the longest run at a word's edges or over
+// several; only when that is none of 31 cells or more are runs inside words
+// looked for.  Returns the pair's count.
+//
+// Bound by instruction issue and, at one wave per SIMD, by its latency: 6 us a
+// round at E = 5 (four pairs) and E = 25 (one).  100k homopolymers of 250 bp with
+// two or three edits at E = 5 / 10 / 25, every pair of which comes here: 988 / 1181 /
+// 1279 us with one pair a wave and its words loaded and compared again in every
+// pass, 218 / 364 / 617 now (extraction over all diagonals with a lane per pair:
+// 212 / 443 / 966; 400k in tandem repeats 524 / 1100 / 2190 to 666 / 1176 / 2920 here).
+// The words of free cells in registers, unrolled over 16, took 335 / 644 / 882.
+template <int G>
+__device__ __forceinline__ uint32_t magnet_by_diagonals(const uint64_t* pair, uint32_t m, uint32_t E, int lane, uint32_t* x) {
+    const int W = (int)((m + 31u) >> 5), i = lane & (G - 1), d = i - (int)E;
+    const uint32_t sh = (uint32_t)d & 31u;
+    const bool pos = d >= 0, on = i <= 2 * (int)E;
+    const int words = __builtin_amdgcn_readfirstlane((int)group_max<64>((uint32_t)W));
+    uint32_t live = 0;   // words with a free cell on some lane
+    uint64_t prev = 0, cur = pair[0];
+    for (int k = 0; k < words; ++k) {
+        const uint64_t next = k + 1 < W ? pair[2 * (k + 1)] : 0ull, ref = pair[2 * k + 1];
+        const uint32_t vp = vacant_word(k - 1, (int)m), vc = vacant_word(k, (int)m), vn = vacant_word(k + 1, (int)m);
+        const uint64_t a = pos ? cur : prev, b = pos ? next : cur;
+        const uint32_t lo = funnel((uint32_t)b, (uint32_t)a, sh), hi = funnel((uint32_t)(b >> 32), (uint32_t)(a >> 32), sh);
+        const uint32_t v = funnel(pos ? vn : vc, pos ? vc : vp, sh);
+        const uint32_t w = on ? ~((lo ^ (uint32_t)ref) | (hi ^ (uint32_t)(ref >> 32)) | v | vc) : 0u;
+        x[64 * k] = w;
+        live |= wave_any(w != 0u) ? 1u << k : 0u;
+        prev = cur;
+        cur = next;
     }
-    return min(m - covered, E + 1u);
+    // f(k, word k), the next live word on its way.
+    auto each_live = [&](auto f) {
+        uint32_t rest = live, k = rest ? (uint32_t)__builtin_ctz(rest) : 0u, ahead = x[64 * k];
+        while (rest != 0u) {
+            const uint32_t w = ahead, at = k;
+            rest &= rest - 1u;
+            k = rest ? (uint32_t)__builtin_ctz(rest) : at;
+            ahead = x[64 * k];
+            f(at, w);
+        }
+    };
+    bool open = m != 0u, rejected = false;
+    uint32_t covered = 0, it = 0, from = 0, upto = 0;   // columns [from, upto) leave the search
+    while (wave_any(open)) {
+        uint32_t best = 0, carry = 0, next = 0;
+        each_live([&](uint32_t k, uint32_t old) {
+            if (k != next) {
+                best = max(best, ival(32u * next - carry, carry));
+                carry = 0;
+            }
+            next = k + 1u;
+            const uint32_t w = old & ~cols_mask((int)k, from, upto);
+            x[64 * k] = w;
+            if (!wave_any(w != 0u)) live ^= 1u << k;
+            const uint32_t head = min((uint32_t)__builtin_ffs((int)~w) - 1u, 32u);
+            best = max(best, ival(32u * k - carry, carry + head));
+            carry = w == ~0u ? carry + 32u : (uint32_t)__builtin_clz(~w);
+        });
+        best = max(best, ival(32u * next - carry, carry));
+        best = group_max<G>(best);
+        if (wave_any(open && ival_len(best) < 31u)) {
+            each_live([&](uint32_t k, uint32_t w) {
+                uint32_t L, s;
+                word_longest(w, L, s);   // (a full word: 31, less than the run it is part of)
+                best = max(best, ival(32u * k + s, L));
+            });
+            best = group_max<G>(best);
+        }
+        const uint32_t L = ival_len(best), s = ival_start(best);
+        if (L == 0u) {
+            open = false;
+        } else if (open) {
+            ++it;
+            covered += L;
+            from = s > 0u ? s - 1u : 0u;
+            upto = s + L + 1u;
+            rejected = covered + (E + 1u - it) * L + E < m;
+            open = !rejected && it <= E;
+        }
+        if constexpr (G == 64) {
+            from = (uint32_t)__builtin_amdgcn_readfirstlane((int)from);
+            upto = (uint32_t)__builtin_amdgcn_readfirstlane((int)upto);
+        }
+    }
+    return rejected ? E + 1u : min(m - covered, E + 1u);
 }
 
 template <int EMAX>
@@ -336,20 +401,93 @@ __global__ void __launch_bounds__(64) magnet_kernel(FilterParams P, uint32_t K) 
             P.cnt[0][id] = (uint16_t)count;
             if (count <= E) atomicOr(&acc[at >> 5], 1u << (at & 31u));
         }
-        for (uint64_t rest = __ballot(together); rest != 0ull; rest &= rest - 1) {
-            const int src = __builtin_ctzll(rest);
-            const uint32_t jm = (uint32_t)__shfl((int)m, src), jE = (uint32_t)__shfl((int)E, src);
-            const uint64_t jo = ((uint64_t)(uint32_t)__shfl((int)(off >> 32), src) << 32) | (uint32_t)__shfl((int)(uint32_t)off, src);
-            const uint32_t count = magnet_pair_by_wave(P.reads + jo, P.refs + jo, jm, jE, lane);
-            if (lane == src) {
-                P.cnt[0][id] = (uint16_t)count;
-                if (count <= E) atomicOr(&acc[at >> 5], 1u << (at & 31u));
+        // The pairs left, 64 / G at a time: lane i of a group loads words i of
+        // its pair (a round ahead), which the group then reads from the LDS.
+        constexpr int G = D <= 16 ? 16 : (D <= 32 ? 32 : 64);
+        constexpr uint32_t WORDS = PAF_MAX_LEN / 32;
+        static_assert(G >= WORDS && CAP >= WORDS + 4, "a lane per word; a pair's words and its diagonals' in the intervals' place");
+        uint64_t* const staged = reinterpret_cast<uint64_t*>(iv + 64 * WORDS);   // [64][read, reference]
+        uint64_t rest = __ballot(together), wr = 0, wf = 0;
+        uint32_t jm = 0, jE = 0, jat = 0;
+        auto fetch = [&]() {
+            int src = -1;   // lane whose pair this one's group takes
+#pragma unroll
+            for (int j = 0; j < 64 / G; ++j) {
+                if (rest != 0ull && lane / G == j) src = __builtin_ctzll(rest);
+                rest &= rest - 1;
+            }
+            const int of = max(src, 0);
+            const uint64_t jo = ((uint64_t)(uint32_t)__shfl((int)(off >> 32), of) << 32) | (uint32_t)__shfl((int)(uint32_t)off, of);
+            jm = (uint32_t)__shfl((int)m, of);
+            jE = (uint32_t)__shfl((int)E, of);
+            jat = (uint32_t)__shfl((int)at, of);
+            if (src < 0) jm = 0;
+            const uint32_t word = (uint32_t)lane % G;
+            wr = wf = 0;
+            if (word < ((jm + 31u) >> 5)) {
+                wr = P.reads[jo + word];
+                wf = P.refs[jo + word];
+            }
+        };
+        bool more = rest != 0ull;
+        if (more) fetch();
+        while (more) {
+            wave_lds_sync();
+            staged[2 * lane] = wr;
+            staged[2 * lane + 1] = wf;
+            wave_lds_sync();
+            const uint32_t gm = jm, gE = jE, gat = jat;
+            more = rest != 0ull;
+            if (more) fetch();
+            const uint32_t count = magnet_by_diagonals<G>(staged + 2 * (lane / G * G), gm, gE, lane, iv + lane);
+            if (gm != 0u && lane % G == 0) {
+                P.cnt[0][slot0 + gat] = (uint16_t)count;
+                if (count <= gE) atomicOr(&acc[gat >> 5], 1u << (gat & 31u));
             }
         }
         wave_lds_sync();
     }
     wave_lds_sync();
     for (uint32_t j = (uint32_t)lane; 32u * j < n_here; j += 64) P.acc[0][(slot0 >> 5) + j] = acc[j];
+}
+
+// max_E 0: the one run that counts is the main diagonal's, all of it, so a pair
+// is accepted when its words are equal.  Bound by HBM: 1M pairs of 250 bp, 128
+// MB, 20.5 us (6.2 TB/s), where SneakySnake takes 20 to 51 us, the more the longer
+// unequal pairs agree.
+__global__ void __launch_bounds__(256) magnet_exact_kernel(FilterParams P) {
+    const int lane = threadIdx.x & 63;
+    const uint64_t tile = (uint64_t)blockIdx.x * 4u + (threadIdx.x >> 6);
+    if (tile >= P.n_tiles) return;
+    uint64_t off;
+    const PairSlot ps = load_slot<true>(P, tile, lane, off);
+    const uint64_t* rd = P.reads + off;
+    const uint64_t* rf = P.refs + off;
+    const uint32_t last = max(ps.W, 1u) - 1u, tail = (1u << (ps.m & 31u)) - 1u;
+    const uint64_t keep = tail ? ((uint64_t)tail << 32) | tail : ~0ull;
+    uint64_t diff = 0;
+    if (!wave_any(ps.W < 2)) {
+        // Two words a load (the last two again past the end).
+        for (uint32_t k = 0; wave_any(diff == 0ull && k <= last); k += 8) {
+            u64x2 a[4], b[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                a[j] = *reinterpret_cast<const u64x2*>(rd + min(k + 2 * j, last - 1u));
+                b[j] = *reinterpret_cast<const u64x2*>(rf + min(k + 2 * j, last - 1u));
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j)
+                diff |= (a[j][0] ^ b[j][0]) | ((a[j][1] ^ b[j][1]) & (k + 2 * j + 1u >= last ? keep : ~0ull));
+        }
+    } else {
+        for (uint32_t k = 0; wave_any(ps.valid && diff == 0ull && k <= last); ++k) {
+            const uint32_t at = ps.valid ? min(k, last) : 0u;
+            diff |= (rd[at] ^ rf[at]) & (k >= last ? keep : ~0ull);
+        }
+    }
+    const uint64_t bal = __ballot(ps.valid && diff == 0ull);
+    if (ps.in_batch) P.cnt[0][ps.slot] = ps.valid && diff != 0ull ? 1 : 0;
+    if (lane < 2 && tile * 64 + 32u * lane < P.n_pairs) P.acc[0][2 * tile + lane] = lane ? (uint32_t)(bal >> 32) : (uint32_t)bal;
 }
 
 const void* magnet_kernel_for(int emax) {
@@ -365,6 +503,11 @@ const void* magnet_kernel_for(int emax) {
 }
 
 }  // namespace
+
+hipError_t launch_magnet_exact(const FilterParams& p, hipStream_t s) {
+    magnet_exact_kernel<<<dim3((p.n_tiles + 3) / 4), dim3(256), 0, s>>>(p);
+    return hipGetLastError();
+}
 
 hipError_t launch_magnet(const FilterParams& p, int emax, int num_cus, hipStream_t s) {
     const void* k = magnet_kernel_for(emax);

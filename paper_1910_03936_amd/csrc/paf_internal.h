@@ -123,6 +123,8 @@ hipError_t launch_verify(const FilterParams& p, int emax, const uint32_t* sel, u
 // p.acc[0] (p.cnt[0] and p.acc[0] hold SneakySnake's, which are right for the
 // others).
 hipError_t launch_magnet(const FilterParams& p, int emax, int num_cus, hipStream_t s);
+// ... and of every pair of a batch with max_E 0.
+hipError_t launch_magnet_exact(const FilterParams& p, hipStream_t s);
 
 // mlp.hip
 struct MlpDev {
