@@ -147,10 +147,12 @@ paf_status paf_pack_ascii(const char* seqs, uint32_t row_stride, const uint16_t*
  * SneakySnake's greedy traversal (Ch. 8, Sec. 8.4), GateKeeper's Hamming
  * fast path plus amended shifted masks (Ch. 5, Sec. 5.2) and Shouji's
  * sliding-window search (Ch. 6, Sec. 6.2).  filters: mask of PAF_* bits.
- * SneakySnake alone: batches with per-pair lengths, thresholds or offsets, and
- * the others up to 1,048,576 pairs, run on the flow engine (each lane's window
- * at its own snake's column, a lane taking its next pair as soon as one is
- * decided); larger ones on the compacting engine (see paf_layout's
+ * SneakySnake alone: small batches (up to about a million pairs, and to two to
+ * four million, or any number, with per-pair arrays, by length and threshold) run
+ * on the flow engine (each lane's window at its own snake's column, a lane taking
+ * its next pair as soon as one is decided); larger ones on the compacting engine
+ * (larger ones with per-pair lengths on either, as a sample of the lengths
+ * decides on the device; see paf_layout's
  * chunk_tiles; up to max_E 15 a first pass of 2 windows, then: up to max_E
  * 3, 4 waves per block, chunks of 4 tiles and later passes of 3 windows;
  * 4..6: 2 waves, 4 tiles, 3 windows; 7..8: 2 waves, 6 tiles, 2 windows;

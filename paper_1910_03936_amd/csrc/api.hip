@@ -326,9 +326,12 @@ paf_layout layout_for(paf_ctx* ctx, const FilterParams& p, int emax, bool queue_
 // engine, the latter as a full grid of chunks.  A forced layout sets its chunk
 // size and block shape, or turns it off.
 paf_status launch_snake(paf_ctx* ctx, FilterParams& p, int emax, const paf_layout* forced, hipStream_t stream) {
-    if (!forced && flow_serves(p)) {
-        PAF_HIP(launch_flow(p, emax, ctx->num_cus, stream), "filter launch");
-        return PAF_OK;
+    if (!forced) {
+        const SnakeEngine on = snake_engine(p, emax);
+        if (on == SnakeEngine::Sampled) p.pick = kPickMixed;
+        if (on != SnakeEngine::Compacting) PAF_HIP(launch_flow(p, emax, ctx->num_cus, stream), "filter launch");
+        if (on == SnakeEngine::Flow) return PAF_OK;
+        if (on == SnakeEngine::Sampled) p.pick = kPickAlike;
     }
     const paf_layout L = forced ? *forced : plain_layout(emax);
     Engine eng = Engine::Snake;

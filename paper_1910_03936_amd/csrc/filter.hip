@@ -781,6 +781,8 @@ __global__ void __launch_bounds__(512)
 __attribute__((amdgpu_waves_per_eu(LPP == 2 ? 4 : (EMAX <= 8 ? 5 : (PART == kPartNarrow ? (EMAX <= 10 ? 4 : 1) : ((EMAX == 20 || EMAX == 31) ? 4 : 1))))))
 chunk_kernel(FilterParams P) {
     extern __shared__ uint64_t lds[];
+    if constexpr (GENERAL && PART == kPartNone && LPP == 1)
+        if (P.pick == kPickAlike && lengths_differ(P, threadIdx.x & 63)) return;
     using DT = typename ChunkDead<EMAX, LPP>::T;
     const int lane = threadIdx.x & 63;
     // Wave-uniform, so the LDS pointers below live in scalar registers.

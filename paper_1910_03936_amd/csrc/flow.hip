@@ -1,6 +1,6 @@
-// SneakySnake of batches with per-pair lengths, thresholds or offsets, and of
-// batches up to kFlowTiles tiles (Ch. 8, Sec. 8.4): one lane per pair, every
-// lane's 32-column window starting at its own snake's column.
+// SneakySnake of small batches and of most with per-pair lengths (Ch. 8, Sec.
+// 8.4; which ones: snake_engine): one lane per pair, every lane's 32-column
+// window starting at its own snake's column.
 //
 // A wave owns every `waves`-th tile of the batch (so that the whole grid walks
 // the batch front to back) and its lanes take the pairs in order: a lane whose
@@ -17,12 +17,11 @@
 // bound it: eight waves per CU run no slower than sixteen.  So it is the
 // faster one where a batch is too small to fill the chip with the compacting
 // engine's chunks, whose waves walk four to six tiles one after another (250
-// bp, E = 10: 100k pairs 49 -> 18.5 us, 1M pairs 83 -> 71 us, but 2M pairs
-// 121 -> 125 us and 10M pairs 470 -> 584 us; E = 0 at 1M 28.8 -> 24.6, E = 31
-// at 1M pairs of 400 bp 460 -> 360 us), and where lengths and thresholds
-// differ from lane to lane, so that a group of 64 pairs is as slow as its
-// longest (uneven mix: 20k pairs 66 -> 18, 200k 79 -> 36, 2M 188 -> 147, 5M
-// 376 -> 330 us).
+// bp, E = 10: 100k pairs 46 -> 18 us, 1M pairs 85 -> 71 us, but 2M pairs 121 ->
+// 125 us and 10M pairs 470 -> 584 us; E = 0 at 1M 28 -> 25, E = 31 at 1M pairs of
+// 400 bp 463 -> 356 us), and where lengths and thresholds differ from lane to
+// lane, so that a group of 64 pairs is as slow as its longest (uneven mix: 20k
+// pairs 66 -> 18, 200k 79 -> 36, 2M 182 -> 147, 5M 375 -> 330 us).
 #include <algorithm>
 
 #include "paf_flow.h"
@@ -30,9 +29,6 @@
 namespace paf {
 
 namespace {
-
-// Batches of one length and threshold up to this size run here.
-constexpr uint32_t kFlowTiles = 16384;
 
 constexpr uint32_t kRing = 1024;   // counts a wave holds in LDS until their tile is complete
 constexpr uint32_t kMeta = 128;    // GENERAL: pairs whose offset, length and threshold are staged ahead
@@ -74,13 +70,17 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
 }
 
 constexpr int kFlowWaves = 4;   // waves per block
-template <int EMAX, bool GENERAL>
+// SAMPLED: the launch runs only if the batch's lengths differ (a kernel of its own:
+// with the question in the general one its loop ran 2 to 5% slower).
+template <int EMAX, bool GENERAL, bool SAMPLED = false>
 __global__ void __launch_bounds__(64 * kFlowWaves) __attribute__((amdgpu_waves_per_eu(EMAX <= 5 ? 8 : 4)))
 flow_kernel(FilterParams P) {
     constexpr int D = 2 * EMAX + 1;
     using DT = typename DeadMask<EMAX>::T;
     __shared__ FlowLds<GENERAL> lds[kFlowWaves];
     const int lane = threadIdx.x & 63;
+    if constexpr (SAMPLED)
+        if (!lengths_differ(P, lane)) return;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     FlowLds<GENERAL>& L = lds[wave];
     // The wave's share: tiles first, first + waves, first + 2 waves, ...
@@ -221,11 +221,11 @@ flow_kernel(FilterParams P) {
     flush(n_here);
 }
 
-template <bool GENERAL>
+template <bool GENERAL, bool SAMPLED = false>
 const void* flow_kernel_for(int emax) {
     switch (emax) {
 #define PAF_CASE(X) \
-    case X: return reinterpret_cast<const void*>(&flow_kernel<X, GENERAL>);
+    case X: return reinterpret_cast<const void*>(&flow_kernel<X, GENERAL, SAMPLED && (X < 20)>);
         PAF_CASE(0) PAF_CASE(1) PAF_CASE(2) PAF_CASE(3) PAF_CASE(4) PAF_CASE(5) PAF_CASE(6)
         PAF_CASE(7) PAF_CASE(8) PAF_CASE(10) PAF_CASE(12) PAF_CASE(15) PAF_CASE(20) PAF_CASE(25)
         PAF_CASE(31)
@@ -236,8 +236,37 @@ const void* flow_kernel_for(int emax) {
 
 }  // namespace
 
-bool flow_serves(const FilterParams& p) {
-    return p.len || p.E || p.word_offset || p.n_tiles <= kFlowTiles;
+// Rows of more words than this take a wave's share of the L1 with them: 64 lanes
+// read two rows each, and four waves per SIMD evict one another's.
+constexpr uint32_t kNarrowWords = 6;
+
+// The largest batches that run here, from both engines' times (us, this one and
+// the compacting one, 70% unrelated pairs and in brackets none).
+//   Uniform: 16384 tiles, so that nothing is slower than the compacting engine in
+// its own chunks: 1M pairs, 250 bp, E = 0 25 / 28 (51 / 82), E = 10 72 / 85 (137 /
+// 151); 100 bp, E = 5 22 / 26 (38 / 39).  13312 where wide rows meet E = 4 to 6 (250
+// bp, E = 5, 850k 31 / 36 (72 / 71), 1M 36 / 38 (93 / 76)) and where the threshold
+// belongs to a lower class, whose general kernel is the slower one here (250 bp,
+// E = 20 as 25, 1M 209 / 197).  (Chunks fitted to the batch as in api.hip take 68
+// (105) at 1M and E = 10 and 39 (55) at 500k, less than this engine's 72 (137)
+// and 43 (69), but 65 (103) at 700k, more than its 52 (91).)
+//   Offsets or thresholds per pair, one length: to where lanes that are alike
+// stop gaining.  250 bp: E = 3 4M 134 / 134, 8M 264 / 249; E = 5 500k 29 / 30, 1M 44 /
+// 42; E = 10 2M 129 / 137, 4M 248 / 236; E = 25 4M 795 / 861; 150 bp, E = 7 8M 243 / 262.
+//   Lengths per pair: mixes gain at every size (5M of the uneven mix, thresholds
+// of 2% / 5% 155 / 191 and 330 / 375), lengths that are alike lose in large batches
+// (all 250 bp, 10M at E = 10 588 / 526, 8M at E = 5 336 / 273), so above 32768
+// tiles a launch of each engine asks 64 of the pairs which of them it is for:
+// 4 us on 100 and more.
+SnakeEngine snake_engine(const FilterParams& p, int emax) {
+    const bool wide = p.wmax > kNarrowWords, per_pair = p.len || p.E || p.word_offset;
+    uint32_t most;   // tiles
+    if (!per_pair) most = (wide && emax >= 4 && emax <= 6) || (int)p.uniform_E <= emax_below(emax) ? 13312u : 16384u;
+    else if (emax >= 20 || (!wide && (emax >= 7 || emax <= 3))) most = ~0u;
+    else if (emax <= 3) most = 65536u;
+    else if (emax <= 6 && wide && !p.len) most = 8192u;
+    else most = 32768u;
+    return p.n_tiles <= most ? SnakeEngine::Flow : p.len ? SnakeEngine::Sampled : SnakeEngine::Compacting;
 }
 
 hipError_t launch_flow(FilterParams p, int emax, int num_cus, hipStream_t stream) {
@@ -245,15 +274,20 @@ hipError_t launch_flow(FilterParams p, int emax, int num_cus, hipStream_t stream
     // class and the one below, and load two words at a time.
     const bool general = p.len || p.E || p.word_offset || words_for(p.uniform_len) < 2 ||
                          (int)p.uniform_E <= emax_below(emax);
-    const void* k = general ? flow_kernel_for<true>(emax) : flow_kernel_for<false>(emax);
+    const void* k = p.pick == kPickMixed ? flow_kernel_for<true, true>(emax)
+                    : general            ? flow_kernel_for<true>(emax)
+                                         : flow_kernel_for<false>(emax);
     if (!k) return hipErrorInvalidValue;
-    // Two waves per SIMD: more only evict each other's rows from the L1 (250
-    // bp, E = 5, 1M pairs: 36 us, 68 with four; E = 10: 71.5 and 71.4).  Mixed
-    // lengths and thresholds take up to four once every wave keeps four tiles
-    // (uneven mix, 200k pairs: 36 us, 44 with four; 5M: 386 and 330).
+    // Two waves per SIMD, and up to `most` once every wave keeps four tiles.
+    // (250 bp, E = 5, 1M pairs: 36 us with two, 68 with four; 100 bp 48 and 38 when
+    // all are related; 2M of the uneven mix with thresholds of 2% 67 with two or
+    // three, 81 with four, of 5% 158, 148 and 147.)
     const uint64_t simds = (uint64_t)num_cus * 4;
-    uint64_t waves = 2 * simds;
-    if (general) waves = std::max(waves, std::min<uint64_t>(4 * simds, p.n_tiles / 4));
+    const bool per_pair = p.len || p.E || p.word_offset;
+    uint64_t most = 4;
+    if (!per_pair) most = p.wmax <= kNarrowWords && p.n_tiles >= 14 * simds ? 4 : 2;
+    else if (p.wmax > kNarrowWords && emax <= 6) most = emax <= 3 ? 2 : 3;
+    const uint64_t waves = std::max(2 * simds, std::min<uint64_t>(most * simds, p.n_tiles / 4));
     p.waves = (uint32_t)std::min<uint64_t>(waves, p.n_tiles);
     // The probes of a window: E + 1 obstacles in as few windows of at most
     // seven as hold them (a window of random bases holds seven to eight);

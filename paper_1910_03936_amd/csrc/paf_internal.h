@@ -46,7 +46,12 @@ struct FilterParams {
     uint32_t part_cap;         // ... and the most obstacles one sub-maze counts (~0u: no cap)
     uint32_t waves;            // flow engine: waves of the launch
     uint32_t probes;           // flow engine: probes per window
+    uint32_t pick;             // kPickAll, or one of two launches of which the batch's lengths pick one
 };
+
+// FilterParams::pick: the launch filters the batch; it does so only if the pairs
+// differ in length, or only if they do not (paf_tile.h: lengths_differ).
+constexpr uint32_t kPickAll = 0, kPickMixed = 1, kPickAlike = 2;
 
 // Kernel selection.
 // Chunk2: the compacting engine with two lanes per pair (whole maze, max_E 9..31).
@@ -109,9 +114,11 @@ size_t filter_lds_bytes(uint32_t waves_per_block, uint32_t wmax);
 // LDS of a compacting launch (keyed launches sort inside the list itself).
 size_t chunk_lds_bytes(uint32_t waves_per_block, bool general, int emax, uint32_t chunk_tiles, uint32_t lpp);
 
-// flow.hip: SneakySnake with every lane at a column of its own; flow_serves:
-// the batches paf_filter runs there.
-bool flow_serves(const FilterParams& p);
+// flow.hip: SneakySnake with every lane at a column of its own, and which of the
+// batches paf_filter runs there: Sampled, the ones that a launch of each engine
+// is made for, as their lengths, which the host does not see, decide.
+enum class SnakeEngine { Flow, Compacting, Sampled };
+SnakeEngine snake_engine(const FilterParams& p, int emax);
 hipError_t launch_flow(FilterParams p, int emax, int num_cus, hipStream_t stream);
 
 // verify.hip: banded edit distance of the selected pairs (sel: accept-bit

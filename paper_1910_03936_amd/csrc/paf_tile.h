@@ -67,6 +67,21 @@ __device__ __forceinline__ PairSlot load_slot(const FilterParams& P, uint64_t ti
     return s;
 }
 
+// Whether a batch's pairs differ in length so much (by an eighth on average)
+// that lanes at columns of their own pay: judged on 64 pairs spread evenly over
+// the batch, the same ones in every wave, so that all come to one answer.
+__device__ __forceinline__ bool lengths_differ(const FilterParams& P, int lane) {
+    const uint64_t id = P.n_pairs * (2u * (uint32_t)lane + 1u) / 128u;
+    const int words = (int)((min((uint32_t)P.len[id], P.max_len) + 31u) >> 5);
+    int sum = words;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o);
+    int off = abs(64 * words - sum);
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) off += __shfl_xor(off, o);
+    return __builtin_amdgcn_readfirstlane(off * 8 - 64 * sum) >= 0;
+}
+
 constexpr int kStageBatch = 8;
 
 // Stage the tile's words into the wave's LDS rows.
