@@ -140,8 +140,11 @@ paf_layout plain_layout(int emax) {
     return paf_layout{1u, 2u, 0u, 1u, 6u, 4u, 1u};
 }
 
-// Widest sub-mazes that are walked all at once.
-constexpr uint32_t kPartNarrowColumns = 16;
+// Widest sub-mazes that are walked all at once: 16 columns, or 12 where one
+// replication ends each after a probe and the diagonals are many (2M pairs, y = 1,
+// at once and one probe at a time: E = 15, t = 16 202 and 200 us; E = 20, t = 12 340
+// and 348, t = 16 298 and 290; E = 25, t = 16 333 and 306).
+uint32_t part_narrow_columns(uint32_t y, int emax) { return y == 1 && emax >= 20 ? 12u : 16u; }
 
 // Tiles per chunk of a batch too small to give every SIMD four chunks of
 // `most` tiles.  250 bp at E = 10 (SneakySnake alone), chunks of 1 / 2 / 4 / 6
@@ -642,7 +645,7 @@ paf_status paf_filter_partitioned(paf_ctx* ctx, const paf_batch* batch, uint32_t
     // E = 10 take 115 / 232 us at t = 5, 125 / 190 at t = 10, 127 / 153 at
     // t = 16, 156 / 167 at t = 25 and 163 / 160 at t = 50; 1M at E = 25 218 / 303
     // at t = 10, 225 / 248 at t = 16 and 282 / 277 at t = 25.
-    const Engine eng = t <= kPartNarrowColumns ? Engine::ChunkPart : Engine::ChunkPartWide;
+    const Engine eng = t <= part_narrow_columns(y, emax) ? Engine::ChunkPart : Engine::ChunkPartWide;
     LaunchShape sh;
     sh.waves_per_block = PL.waves_per_block;
     sh.lds_bytes = chunk_lds_bytes(sh.waves_per_block, general, emax, p.chunk, 1);

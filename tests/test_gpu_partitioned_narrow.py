@@ -37,3 +37,16 @@ def test_chunk_sizes(gpu_ctx, per_pair):
         a, c = oracle.sneakysnake_t_batch(p.reads, p.refs, p.len, p.E, 8)
         assert_parity(results(gpu_ctx.filter_partitioned(b, 8), n), {SS: (a, c)}, f"n={n}")
     gpu_ctx.check()
+
+
+@pytest.mark.parametrize("E", [15, 16, 31])
+def test_widest_narrow_form(gpu_ctx, E):
+    # One replication: the form changes after 12 columns from the class of 20 on.
+    for per_pair in (False, True):
+        w = pairgen.UNEVEN_MIX if per_pair else pairgen.FIXED_250BP.with_E(E)
+        p = pairgen.generate(w, 77, 64 * 7 + 9)
+        b = to_device(p, gpu_ctx, per_pair=per_pair, offsets=per_pair, max_E=E)
+        for t in (12, 13, 16, 17):
+            a, c = oracle.sneakysnake_fpga_batch(p.reads, p.refs, p.len, p.E, t, 1)
+            assert_parity(results(gpu_ctx.filter_partitioned(b, t, 1), p.n), {SS: (a, c)}, f"E={E} t={t} {per_pair}")
+    gpu_ctx.check()
