@@ -54,9 +54,10 @@ constexpr uint32_t kVerifyTiles = 32;
 // and 16 measured the same, 32 7% slower).
 constexpr int kRefill = 16;
 // Waves per SIMD that a launch aims at: one / two / three / four take 81 / 71 / 72 / 72 us
-// for 4M pairs at E = 10 and 20 / 18.6 / 15.6 / 14.9 us for 4M of 100 bp at
-// E = 3; fewer where the LDS holds fewer.
-constexpr uint32_t kVerifyWaves = 3;
+// for 4M pairs at E = 10 and 20 / 18.6 / 15.6 / 14.9 us for 4M of 100 bp at E = 3,
+// and three / four 147 / 131 us for 4M of 100 bp at E = 5, all selected (138 with a
+// lane per pair in step); fewer where the LDS holds fewer.
+constexpr uint32_t kVerifyWaves = 4;
 
 // Rows of F: diagonals -emax - 1 .. emax + 1.
 __host__ __device__ constexpr uint32_t reach_rows(uint32_t emax) { return 2 * emax + 3; }
