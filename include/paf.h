@@ -439,7 +439,14 @@ typedef struct {
  * paf_filter_bucketed_local for SneakySnake alone, paf_filter_bucketed for
  * other masks), and its decisions are copied back into host_out
  * (paf_out with [host] pointers: accept bits and counts for all n pairs).
- * Blocks until every chunk is done.  Decisions equal paf_filter's. */
+ * Blocks until every chunk is done.  Decisions equal paf_filter's.
+ * Three streams, their events and the two device buffers (which hold two
+ * chunks' words, lengths, thresholds, offsets and outputs) stay with the context
+ * for its next streamed batch, up to 2 GiB, until paf_destroy; larger buffers
+ * are given back when the call ends.  Buffers that are too small are made anew,
+ * for the shapes of earlier batches too where that stays within 2 GiB and the
+ * memory suffices, else for this call's alone: PAF_ERR_NOMEM only if those do
+ * not fit. */
 paf_status paf_stream_filter(paf_ctx* ctx, const paf_host_batch* batch, uint64_t chunk_pairs,
                              uint32_t filters, int learned, const paf_out* host_out,
                              paf_stream_stats* stats);

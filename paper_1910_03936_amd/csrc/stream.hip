@@ -145,7 +145,44 @@ namespace {
 
 constexpr size_t kStreamKeepBytes = (size_t)2 << 30;
 
-// A slot for chunks of `pairs` pairs and `words` words per array.
+// Bytes of both slots for chunks of `pairs` pairs and `words` words per array.
+size_t slots_bytes(uint64_t words, uint64_t pairs, uint32_t filters) {
+    const uint64_t nsb = (pairs + kScanBlock - 1) / kScanBlock;
+    const uint64_t stages = (uint64_t)__builtin_popcount(filters);
+    return 2 * (words * 16 + pairs * 11 + nsb * 12 + stages * (pairs / 8 + pairs * 2));
+}
+
+// The slots' buffers made anew; false (and none) if the memory does not suffice.
+bool make_slots(StreamWs* w, uint64_t words, uint64_t pairs, uint32_t filters) {
+    for (auto& s : w->slots) free_buffers(s);
+    w->words = w->pairs = 0;
+    w->filters = 0;
+    w->bytes = 0;
+    const uint64_t nsb = (pairs + kScanBlock - 1) / kScanBlock;
+    for (auto& s : w->slots) {
+        bool ok = hipMalloc(&s.rd, words * 8) == hipSuccess && hipMalloc(&s.rf, words * 8) == hipSuccess &&
+                  hipMalloc(&s.len, pairs * 2) == hipSuccess && hipMalloc(&s.E, pairs) == hipSuccess &&
+                  hipMalloc(&s.off, pairs * 8) == hipSuccess && hipMalloc(&s.sums, nsb * 4) == hipSuccess &&
+                  hipMalloc(&s.base, nsb * 8) == hipSuccess;
+        for (int f = 0; f < 3 && ok; ++f)
+            if ((filters >> f) & 1u)
+                ok = hipMalloc(&s.acc[f], pairs / 8) == hipSuccess && hipMalloc(&s.cnt[f], pairs * 2) == hipSuccess;
+        if (!ok) {
+            (void)hipGetLastError();
+            for (auto& t : w->slots) free_buffers(t);
+            return false;
+        }
+    }
+    w->words = words;
+    w->pairs = pairs;
+    w->filters = filters;
+    w->bytes = slots_bytes(words, pairs, filters);
+    return true;
+}
+
+// Slots for chunks of `pairs` pairs and `words` words per array: the kept ones,
+// or new ones that fit the earlier shapes too while those can be kept, or just
+// this call's.
 paf_status ensure_stream_ws(paf_ctx* ctx, uint64_t words, uint64_t pairs, uint32_t filters) {
     StreamWs* w = ctx->stream_ws;
     if (!w) {
@@ -165,36 +202,11 @@ paf_status ensure_stream_ws(paf_ctx* ctx, uint64_t words, uint64_t pairs, uint32
         }
     }
     if (w->words >= words && w->pairs >= pairs && (w->filters & filters) == filters) return PAF_OK;
-    words = std::max(words, w->words);
-    pairs = std::max(pairs, w->pairs);
-    filters |= w->filters;
-    w->words = w->pairs = 0;
-    w->filters = 0;
-    w->bytes = 0;
-    const uint64_t nsb = (pairs + kScanBlock - 1) / kScanBlock;
-    for (auto& s : w->slots) {
-        free_buffers(s);
-        bool ok = hipMalloc(&s.rd, words * 8) == hipSuccess && hipMalloc(&s.rf, words * 8) == hipSuccess &&
-                  hipMalloc(&s.len, pairs * 2) == hipSuccess && hipMalloc(&s.E, pairs) == hipSuccess &&
-                  hipMalloc(&s.off, pairs * 8) == hipSuccess && hipMalloc(&s.sums, nsb * 4) == hipSuccess &&
-                  hipMalloc(&s.base, nsb * 8) == hipSuccess;
-        w->bytes += words * 16 + pairs * 11 + nsb * 12;
-        for (int f = 0; f < 3 && ok; ++f)
-            if ((filters >> f) & 1u) {
-                ok = hipMalloc(&s.acc[f], pairs / 8) == hipSuccess && hipMalloc(&s.cnt[f], pairs * 2) == hipSuccess;
-                w->bytes += pairs / 8 + pairs * 2;
-            }
-        if (!ok) {
-            (void)hipGetLastError();
-            for (auto& t : w->slots) free_buffers(t);
-            w->bytes = 0;
-            return fail(PAF_ERR_NOMEM, "streaming buffers");
-        }
-    }
-    w->words = words;
-    w->pairs = pairs;
-    w->filters = filters;
-    return PAF_OK;
+    const uint64_t all_words = std::max(words, w->words), all_pairs = std::max(pairs, w->pairs);
+    const uint32_t all_filters = filters | w->filters;
+    if (slots_bytes(all_words, all_pairs, all_filters) <= kStreamKeepBytes && make_slots(w, all_words, all_pairs, all_filters))
+        return PAF_OK;
+    return make_slots(w, words, pairs, filters) ? PAF_OK : fail(PAF_ERR_NOMEM, "streaming buffers");
 }
 
 // Words of pairs [a, b), or UINT64_MAX when a length is outside [1, max_len]
@@ -281,7 +293,8 @@ paf_status paf_stream_filter(paf_ctx* ctx, const paf_host_batch* hb, uint64_t ch
     // has left that stage: the next chunk's words come in while this one is
     // filtered.  (With the results on the stream of the incoming copies, every
     // chunk's copy waited for the previous chunk's filter.)  2M pairs in chunks
-    // of 512k, with the buffers kept: 5.49 -> 3.78 ms, 50 of the link's 57 GB/s.
+    // of 512k: 5.53 ms with two streams, 4.08 on a new context, 3.79 from its
+    // second call on, whose buffers are there: 50 of the link's 57 GB/s.
     double h2d = 0;
     const auto t0 = std::chrono::steady_clock::now();
     for (uint64_t c = 0; c < nchunks && st == PAF_OK; ++c) {
