@@ -679,7 +679,7 @@ paf_status paf_filter_magnet_noalloc(paf_ctx* ctx, const paf_batch* batch, const
     if (st != PAF_OK) return st;
     if ((st = check_out(out, filters)) != PAF_OK) return st;
     if (p.n_pairs > (uint64_t)PAF_MAGNET_NOALLOC_MAX_PAIRS)
-        return fail(PAF_ERR_RANGE, "batch larger than the static workspace (PAF_MAGNET_NOALLOC_MAX_PAIRS pairs)");
+        return fail(PAF_ERR_RANGE, "more than PAF_MAGNET_NOALLOC_MAX_PAIRS pairs (what the call's former static workspace held)");
     const int emax = emax_bucket((int)p.max_E);
     if (emax < 0) return fail(PAF_ERR_RANGE, "max_E exceeds PAF_MAX_E");
     set_outputs(p, out);

@@ -164,16 +164,8 @@ __device__ __forceinline__ ChunkEntry chunk_unpack(uint64_t v) {
 // (only the read positions before 0 are vacant: the low -d bits of diagonal
 // d < 0, a constant), kVacAny from the per-lane vacancy words (short pairs and
 // the last windows).  CONT folds in the dead-diagonal bit of a snake that
-// entered inside a pipe (bit 0 of the window).  v_bitop3 takes s1 | (s0 ^ s2)
-// (truth table 0xDE) and its complement (0x21) in one instruction; both are
-// symmetric in s0 and s2.
+// entered inside a pipe (bit 0 of the window).
 constexpr int kVacNone = 0, kVacFirst = 1, kVacAny = 2;
-__device__ __forceinline__ uint32_t or_xor3(uint32_t a, uint32_t t, uint32_t b) {
-    return __builtin_amdgcn_bitop3_b32(a, t, b, 0xDE);
-}
-__device__ __forceinline__ uint32_t nor_xor3(uint32_t a, uint32_t t, uint32_t b) {
-    return __builtin_amdgcn_bitop3_b32(a, t, b, 0x21);
-}
 
 // a & ~(s ^ h): the bits of a that s left out (h = 0) or has (h = 1).
 __device__ __forceinline__ uint32_t run_to_end(uint32_t a, uint32_t s, uint32_t h) {
@@ -197,17 +189,17 @@ __device__ __forceinline__ void chunk_map(const WindowWords& q, DT dead, uint32_
         }
         uint32_t t;
         if constexpr (VAC == kVacFirst && !CONT && d < 0) {
-            t = or_xor3(lo, (1u << -d) - 1u, q.flo);
+            t = or_xor(lo, (1u << -d) - 1u, q.flo);
         } else if constexpr (VAC == kVacAny || CONT) {
             uint32_t v = 0;
             if constexpr (VAC == kVacAny) v = diag_vacant<d>(q);
             if constexpr (VAC == kVacFirst && d < 0) v = (1u << -d) - 1u;
             if constexpr (CONT) v |= (uint32_t)((dead >> I) & 1u);
-            t = or_xor3(lo, v, q.flo);
+            t = or_xor(lo, v, q.flo);
         } else {
             t = lo ^ q.flo;
         }
-        M[I] = nor_xor3(hi, t, q.fhi);
+        M[I] = nor_xor(hi, t, q.fhi);
         chunk_map<EMAX, VAC, CONT, DT, I + 1>(q, dead, M);
     }
 }
@@ -248,8 +240,8 @@ __device__ __forceinline__ void chunk_map_half(const HalfWords& q, uint32_t dead
         uint32_t v = 0;
         if constexpr (VAC) v = funnel(q.vb, q.va, I);
         if constexpr (CONT) v |= (dead >> I) & 1u;
-        const uint32_t t = (VAC || CONT) ? or_xor3(lo, v, q.flo) : lo ^ q.flo;
-        M[I] = nor_xor3(hi, t, q.fhi);
+        const uint32_t t = (VAC || CONT) ? or_xor(lo, v, q.flo) : lo ^ q.flo;
+        M[I] = nor_xor(hi, t, q.fhi);
         chunk_map_half<EMAX, VAC, CONT, I + 1>(q, dead, M);
     }
 }

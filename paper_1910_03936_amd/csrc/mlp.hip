@@ -60,15 +60,6 @@ __device__ __forceinline__ bf16x8 a1_at(const uint16_t* sW1, int mt, int kt, int
     return *reinterpret_cast<const bf16x8*>(&sW1[((mt * 2 + kt) * 64 + lane) * 8]);
 }
 
-// Hidden index carried by element j of lane group g in layer-2 k-tile kt.
-// Layer 1 leaves hidden units 16 mt + 4 g + i (i = 0..3) of m-tile mt in lane
-// group g; pairing m-tiles 2 kt and 2 kt + 1 gives each lane the 8 k-values of
-// a layer-2 fragment without moving data.  A and B use the same order, so the
-// dot products are unchanged.
-__host__ __device__ __forceinline__ int l2_hidden(int kt, int g, int j) {
-    return 32 * kt + (j < 4 ? 4 * g + j : 16 + 4 * g + (j - 4));
-}
-
 // ---------------------------------------------------------------------------
 // Working copies of the weights: bf16 row-major W1 [h][f], W2 [o][h] and its
 // transpose, W3 rounded to bf16 values, and matrix-core fragment orders.
@@ -84,7 +75,11 @@ __device__ __forceinline__ void store_working_copies(uint32_t i, float w, uint16
         const uint32_t x = i - OFF_W2, o = x / kHid, h = x % kHid;
         w2b[x] = v;
         w2tb[h * kHid + o] = v;
-        // The element and lane group that l2_hidden gives hidden unit h.
+        // Layer 1 leaves hidden units 16 mt + 4 g + i (i = 0..3) of m-tile mt in
+        // lane group g; pairing m-tiles 2 kt and 2 kt + 1 gives each lane the 8
+        // k-values of a layer-2 fragment without moving data, elements 0 to 3 of
+        // the first and 4 to 7 of the second.  A and B use the same order, so the
+        // dot products are unchanged.
         const uint32_t kt = h >> 5, r = h & 31u, g = (r & 15u) >> 2, j = (r & 3u) + (r >= 16u ? 4u : 0u);
         w2f[(((o >> 4) * 4 + kt) * 64 + g * 16 + (o & 15u)) * 8 + j] = v;
     } else if (i >= (uint32_t)OFF_W3 && i < (uint32_t)OFF_B3) {
@@ -237,10 +232,6 @@ __device__ __forceinline__ void pack_row(const float* v, uint4 (&row)[NF / 8]) {
 // long, every lane's E >= EF): blocked-cell counts of the first two windows
 // straight from the packed words, converted to the bf16 inputs and stored
 // as the pair's staged row.
-__device__ __forceinline__ uint32_t or_xor3_m(uint32_t a, uint32_t t, uint32_t b) {
-    return __builtin_amdgcn_bitop3_b32(a, t, b, 0xDE);   // t | (a ^ b)
-}
-
 template <int EF, int K, int I = 0>
 __device__ __forceinline__ void blocked_counts(uint32_t plo, uint32_t phi, uint32_t clo, uint32_t chi,
                                                uint32_t nlo, uint32_t nhi, uint32_t flo, uint32_t fhi,
@@ -260,7 +251,7 @@ __device__ __forceinline__ void blocked_counts(uint32_t plo, uint32_t phi, uint3
         }
         uint32_t t = lo ^ flo;
         if constexpr (K == 0) t |= left_vacant<d>();
-        z[I] += __builtin_popcount(or_xor3_m(hi, t, fhi));
+        z[I] += __builtin_popcount(or_xor(hi, t, fhi));
         blocked_counts<EF, K, I + 1>(plo, phi, clo, chi, nlo, nhi, flo, fhi, z);
     }
 }

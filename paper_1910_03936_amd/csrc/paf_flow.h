@@ -8,16 +8,6 @@
 namespace paf {
 namespace {
 
-__device__ __forceinline__ uint32_t or_xor(uint32_t a, uint32_t t, uint32_t b) {   // t | (a ^ b)
-    return __builtin_amdgcn_bitop3_b32(a, t, b, 0xDE);
-}
-__device__ __forceinline__ uint32_t nor_xor(uint32_t a, uint32_t t, uint32_t b) {  // ~(t | (a ^ b))
-    return __builtin_amdgcn_bitop3_b32(a, t, b, 0x21);
-}
-__device__ __forceinline__ uint32_t or3(uint32_t a, uint32_t b, uint32_t c) {
-    return __builtin_amdgcn_bitop3_b32(a, b, c, 0xFE);
-}
-
 // The 32 columns from a lane's column c: read planes of positions c - 32 ..
 // c + 63 (p, c, n), reference planes of columns c .. c + 31, and the vacant
 // read positions (set by flow_vacancy).

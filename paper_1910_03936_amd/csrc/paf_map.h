@@ -16,8 +16,18 @@ __device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t s)
 
 __device__ __forceinline__ uint32_t popc(uint32_t x) { return __builtin_popcount(x); }
 
-// acc | (z & ~y) in one v_bitop3 (truth table 0xF4 with s0 = acc, s1 = z,
-// s2 = y).
+// Three-input logic in one v_bitop3 each (truth table bit s0 * 4 + s1 * 2 + s2).
+__device__ __forceinline__ uint32_t or3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0xFE);
+}
+__device__ __forceinline__ uint32_t or_xor(uint32_t a, uint32_t t, uint32_t b) {   // t | (a ^ b)
+    return __builtin_amdgcn_bitop3_b32(a, t, b, 0xDE);
+}
+__device__ __forceinline__ uint32_t nor_xor(uint32_t a, uint32_t t, uint32_t b) {  // ~(t | (a ^ b))
+    return __builtin_amdgcn_bitop3_b32(a, t, b, 0x21);
+}
+
+// acc | (z & ~y) (truth table 0xF4 with s0 = acc, s1 = z, s2 = y).
 __device__ __forceinline__ uint32_t or_andn(uint32_t acc, uint32_t z, uint32_t y) {
     return __builtin_amdgcn_bitop3_b32(acc, z, y, 0xF4);
 }

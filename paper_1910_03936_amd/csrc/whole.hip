@@ -33,9 +33,6 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
 __device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);
 }
-__device__ __forceinline__ uint32_t or3(uint32_t a, uint32_t b, uint32_t c) {
-    return __builtin_amdgcn_bitop3_b32(a, b, c, 0xFE);
-}
 // One step of a bit-sliced less-than from the low bit up, (~n & o) | (~(n ^ o) & t).
 __device__ __forceinline__ uint32_t lt_step(uint32_t n, uint32_t o, uint32_t t) {
     return __builtin_amdgcn_bitop3_b32(n, o, t, 0x8E);
