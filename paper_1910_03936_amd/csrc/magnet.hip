@@ -100,10 +100,20 @@ constexpr uint32_t magnet_per_window(int emax) { return emax <= 15 ? 2u : 3u; }
 // which nearly all survive.
 constexpr uint64_t kWavesPerSimd = 2;
 
+// Up to this threshold the pairs that SneakySnake found free of obstacles are left
+// out, which are then a large part of the accepted ones (10M related pairs of 250
+// bp at E = 1, half of them equal: 1777 -> 1129 us).
+constexpr int kSkipFree = 3;
+
 // Intervals a lane holds (related pairs have about 2 E; 112 was the most seen
 // for unrelated ones).  The LDS they take bounds the waves of a CU: 128 took
 // 976 us where 80 takes 742 (500k pairs, E = 25).
 __host__ __device__ constexpr uint32_t magnet_intervals(int emax) { return emax <= 10 ? 40u : (emax <= 15 ? 56u : (emax <= 25 ? 80u : 96u)); }
+
+// LDS of a wave, in the 1280-byte units it is allocated in.
+constexpr uint64_t magnet_lds_bytes(int emax) {
+    return (magnet_intervals(emax) * 256 + magnet_tiles(emax) * (8 + 128) + 1279) / 1280 * 1280;
+}
 
 // Interval [s, s + len): longer ones and then smaller starts are larger.
 __device__ __forceinline__ uint32_t ival(uint32_t s, uint32_t len) { return (len << 10) | (1023u - s); }
@@ -135,7 +145,7 @@ __device__ __forceinline__ uint32_t group_max(uint32_t v) {
 // two or three edits at E = 5 / 10 / 25, every pair of which comes here: 988 / 1181 /
 // 1279 us with one pair a wave and its words loaded and compared again in every
 // pass, 218 / 364 / 617 now (extraction over all diagonals with a lane per pair:
-// 212 / 443 / 966; 400k in tandem repeats 524 / 1100 / 2190 to 666 / 1176 / 2920 here).
+// 212 / 443 / 966; 400k in tandem repeats 524 / 1100 / 2190 to 666 / 1177 / 2246 here).
 // The words of free cells in registers, unrolled over 16, took 335 / 644 / 882.
 template <int G>
 __device__ __forceinline__ uint32_t magnet_by_diagonals(const uint64_t* pair, uint32_t m, uint32_t E, int lane, uint32_t* x) {
@@ -227,14 +237,31 @@ __global__ void __launch_bounds__(64) magnet_kernel(FilterParams P, uint32_t K) 
     const uint32_t n_here = (uint32_t)min<uint64_t>((uint64_t)K * 64, P.n_pairs - slot0);
     uint32_t end = 0;
     const uint32_t bits = chunk_bits(P.acc[0], slot0, n_here, lane);
+    for (uint32_t j = (uint32_t)lane; j < 2 * K; j += 64) acc[j] = 0u;
+    wave_lds_sync();
+    constexpr uint32_t AHEAD = 8;   // tiles whose counts are loaded together
+    uint32_t counts[EMAX <= kSkipFree ? AHEAD : 1];
     for (uint32_t g = 0; g < n_here; g += 64) {
         const uint32_t i = g + (uint32_t)lane;
-        const bool take = chunk_bit(bits, g >> 6, lane) && i < n_here;
+        bool take = chunk_bit(bits, g >> 6, lane) && i < n_here;
+        if constexpr (EMAX <= kSkipFree) {
+            // A pair that SneakySnake crossed without an obstacle is one run.
+            const uint32_t t = (g >> 6) % AHEAD;
+            if (t == 0u) {
+#pragma unroll
+                for (uint32_t j = 0; j < AHEAD; ++j) counts[j] = P.cnt[0][slot0 + min(i + 64 * j, n_here - 1u)];
+            }
+            uint32_t c = 0;
+#pragma unroll
+            for (uint32_t j = 0; j < AHEAD; ++j) c = j == t ? counts[j] : c;
+            const uint64_t free = __ballot(take && c == 0u);
+            if (lane < 2) acc[2 * (g >> 6) + lane] = lane ? (uint32_t)(free >> 32) : (uint32_t)free;
+            take = take && c != 0u;
+        }
         const uint64_t bal = __ballot(take);
         if (take) list[end + rank_in(bal)] = (uint16_t)i;
         end += (uint32_t)__builtin_popcountll(bal);
     }
-    for (uint32_t j = (uint32_t)lane; j < 2 * K; j += 64) acc[j] = 0u;
     wave_lds_sync();
 
     for (uint32_t g = 0; g < end; g += 64) {
@@ -452,42 +479,74 @@ __global__ void __launch_bounds__(64) magnet_kernel(FilterParams P, uint32_t K) 
 }
 
 // max_E 0: the one run that counts is the main diagonal's, all of it, so a pair
-// is accepted when its words are equal.  Bound by HBM: 1M pairs of 250 bp, 128
-// MB, 20.5 us (6.2 TB/s), where SneakySnake takes 20 to 51 us, the more the longer
-// unequal pairs agree.
+// is accepted when its words are equal.  Bound by HBM: rows are read as they lie,
+// a word a lane, and a lane whose word differs marks its pair (a lane per pair
+// reads rows apart, whose lines leave the L1 between its loads: 10M pairs of 250
+// bp 307 us, 216 this way).  A wave takes 512 words of a batch of one length, or a
+// tile whose rows are of wmax words.
+constexpr uint32_t kExactTiles = 8;
+__host__ __device__ __forceinline__ uint32_t exact_tiles(bool general, uint32_t stride) {
+    return general || stride >= kExactTiles ? 1u : kExactTiles / stride;
+}
+template <bool GENERAL>
 __global__ void __launch_bounds__(256) magnet_exact_kernel(FilterParams P) {
+    constexpr int B = 8;   // words on their way
+    __shared__ uint32_t marks[4][kExactTiles * 64];
     const int lane = threadIdx.x & 63;
-    const uint64_t tile = (uint64_t)blockIdx.x * 4u + (threadIdx.x >> 6);
+    uint32_t* const differs = marks[threadIdx.x >> 6];
+    const uint32_t T = exact_tiles(GENERAL, P.stride_words);
+    const uint64_t tile = ((uint64_t)blockIdx.x * 4u + (threadIdx.x >> 6)) * T;
     if (tile >= P.n_tiles) return;
-    uint64_t off;
-    const PairSlot ps = load_slot<true>(P, tile, lane, off);
-    const uint64_t* rd = P.reads + off;
-    const uint64_t* rf = P.refs + off;
-    const uint32_t last = max(ps.W, 1u) - 1u, tail = (1u << (ps.m & 31u)) - 1u;
-    const uint64_t keep = tail ? ((uint64_t)tail << 32) | tail : ~0ull;
-    uint64_t diff = 0;
-    if (!wave_any(ps.W < 2)) {
-        // Two words a load (the last two again past the end).
-        for (uint32_t k = 0; wave_any(diff == 0ull && k <= last); k += 8) {
-            u64x2 a[4], b[4];
+    const uint32_t n_here = (uint32_t)min<uint64_t>(64u * T, P.n_pairs - tile * 64);
+    for (uint32_t i = 0; i < T; ++i) differs[64 * i + lane] = 0u;
+    // The bits that count of a pair's last word.
+    auto kept = [](uint32_t m) -> uint64_t {
+        const uint64_t x = (1ull << (m & 31u)) - 1ull;
+        return x ? x << 32 | x : ~0ull;
+    };
+    uint64_t off = 0;
+    PairSlot ps = {};
+    if constexpr (GENERAL) ps = load_slot<true>(P, tile, lane, off);
+    const uint32_t S = GENERAL ? P.wmax : P.stride_words, rows = GENERAL ? 64u : n_here;
+    const uint64_t base = tile * 64 * (uint64_t)S;
+    uint32_t pr = (uint32_t)lane / S, k = (uint32_t)lane - pr * S;
+    const uint32_t dp = 64u / S, dk = 64u - dp * S;
+    wave_lds_sync();
+    while (wave_any(pr < rows)) {
+        uint64_t x[B], y[B], keep[B];
+        uint32_t at[B];
 #pragma unroll
-            for (uint32_t j = 0; j < 4; ++j) {
-                a[j] = *reinterpret_cast<const u64x2*>(rd + min(k + 2 * j, last - 1u));
-                b[j] = *reinterpret_cast<const u64x2*>(rf + min(k + 2 * j, last - 1u));
+        for (int b = 0; b < B; ++b) {
+            uint32_t m = P.uniform_len;
+            uint64_t a = base + (uint64_t)pr * S + k;
+            if constexpr (GENERAL) {
+                const int of = (int)min(pr, 63u);
+                m = (uint32_t)__shfl((int)ps.m, of);   // (0: no pair there, or one out of range)
+                a = ((uint64_t)(uint32_t)__shfl((int)(off >> 32), of) << 32 | (uint32_t)__shfl((int)(uint32_t)off, of)) + k;
             }
+            const uint32_t W = (m + 31u) >> 5;
+            const bool ok = pr < rows && k < W;
+            x[b] = P.reads[ok ? a : 0ull];
+            y[b] = P.refs[ok ? a : 0ull];
+            keep[b] = !ok ? 0ull : k + 1u == W ? kept(m) : ~0ull;
+            at[b] = pr;
+            pr += dp;
+            k += dk;
+            if (k >= S) { k -= S; pr += 1; }
+        }
 #pragma unroll
-            for (uint32_t j = 0; j < 4; ++j)
-                diff |= (a[j][0] ^ b[j][0]) | ((a[j][1] ^ b[j][1]) & (k + 2 * j + 1u >= last ? keep : ~0ull));
-        }
-    } else {
-        for (uint32_t k = 0; wave_any(ps.valid && diff == 0ull && k <= last); ++k) {
-            const uint32_t at = ps.valid ? min(k, last) : 0u;
-            diff |= (rd[at] ^ rf[at]) & (k >= last ? keep : ~0ull);
-        }
+        for (int b = 0; b < B; ++b)
+            if (((x[b] ^ y[b]) & keep[b]) != 0ull) differs[at[b]] = 1u;
     }
-    const uint64_t bal = __ballot(ps.valid && diff == 0ull);
-    if (ps.in_batch) P.cnt[0][ps.slot] = ps.valid && diff != 0ull ? 1 : 0;
-    if (lane < 2 && tile * 64 + 32u * lane < P.n_pairs) P.acc[0][2 * tile + lane] = lane ? (uint32_t)(bal >> 32) : (uint32_t)bal;
+    wave_lds_sync();
+    for (uint32_t i = 0; 64u * i < n_here; ++i) {
+        const uint32_t j = 64u * i + (uint32_t)lane;
+        const bool valid = GENERAL ? ps.valid : j < n_here, diff = differs[j] != 0u;
+        const uint64_t bal = __ballot(valid && !diff);
+        if (j < n_here) P.cnt[0][tile * 64 + j] = valid && diff ? 1 : 0;
+        if (lane < 2 && 64u * i + 32u * lane < n_here)
+            P.acc[0][2 * (tile + i) + lane] = lane ? (uint32_t)(bal >> 32) : (uint32_t)bal;
+    }
 }
 
 const void* magnet_kernel_for(int emax) {
@@ -505,7 +564,11 @@ const void* magnet_kernel_for(int emax) {
 }  // namespace
 
 hipError_t launch_magnet_exact(const FilterParams& p, hipStream_t s) {
-    magnet_exact_kernel<<<dim3((p.n_tiles + 3) / 4), dim3(256), 0, s>>>(p);
+    const bool general = p.len || p.E || p.word_offset;
+    const uint32_t T = exact_tiles(general, p.stride_words);
+    const dim3 grid((uint32_t)(((uint64_t)p.n_tiles + 4 * T - 1) / (4 * T)));
+    if (general) magnet_exact_kernel<true><<<grid, dim3(256), 0, s>>>(p);
+    else magnet_exact_kernel<false><<<grid, dim3(256), 0, s>>>(p);
     return hipGetLastError();
 }
 
@@ -514,6 +577,17 @@ hipError_t launch_magnet(const FilterParams& p, int emax, int num_cus, hipStream
     if (!k) return hipErrorInvalidValue;
     const uint64_t want = (uint64_t)num_cus * 4 * kWavesPerSimd;
     uint32_t K = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(magnet_tiles(emax), p.n_tiles / want));
+    if (emax >= 12 && K > 1) {
+        // The LDS holds eight to six of these waves on a CU: where the last turn
+        // would run few, longer chunks take one turn less (400k homopolymers of
+        // 250 bp at E = 25 2821 -> 2263 us; of the usual mix 1.5M pairs at E = 25
+        // 1816 -> 1443 and 500k at E = 15 291 -> 207).  Not where it would run half (500k
+        // at E = 25 652 -> 689), nor chunks of one tile (140k related pairs 559 -> 627).
+        const uint64_t most = (uint64_t)num_cus * std::min<uint64_t>(4 * kWavesPerSimd, 160 * 1024 / magnet_lds_bytes(emax));
+        const uint64_t chunks = (p.n_tiles + K - 1) / K, turns = chunks / most;
+        if (turns >= 1 && (chunks - turns * most) * 5 < 2 * most)
+            K = (uint32_t)std::min<uint64_t>(magnet_tiles(emax), (p.n_tiles + turns * most - 1) / (turns * most));
+    }
     const uint64_t chunks = (p.n_tiles + K - 1) / K;
     FilterParams arg = p;
     void* args[] = {&arg, &K};

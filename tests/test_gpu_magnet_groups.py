@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import pairgen
@@ -67,3 +68,30 @@ def test_equal_pairs_only(gpu_ctx, lens):
     _check(gpu_ctx, reads, refs, ln, 0, True, f"lens={lens}")
     if len(lens) == 1:
         _check(gpu_ctx, reads, refs, ln, 0, False, f"uniform {lens}")
+
+
+def _repeated(ctx, p, n):
+    """p's pairs over and over, n of them: every repeat gives p's counts and decisions."""
+    b = to_device(p, ctx, per_pair=False, offsets=False)
+    acc, cnt = oracle.magnet_batch(p.reads, p.refs, p.len, p.E)
+    times = -(-n // p.n)
+    big = paf.Batch(b.reads.repeat(times), b.refs.repeat(times), n, b.stride_words, uniform_len=b.uniform_len,
+                    uniform_E=b.uniform_E, max_len=b.max_len, max_E=b.max_E)
+    out = ctx.filter_magnet(big)[paf.SNEAKYSNAKE]
+    ids = torch.arange(n, device="cuda") % p.n
+    assert torch.equal(paf.counts_u16(out[1]).to(torch.int32), torch.from_numpy(cnt.astype(np.int32)).cuda()[ids])
+    assert torch.equal(paf.accept_bits_to_bool(out[0], n), torch.from_numpy(acc.astype(bool)).cuda()[ids])
+    ctx.check()
+
+
+@pytest.mark.parametrize("m,n", [(20, 64 * 8 * 5 + 3), (64, 64 * 4 * 9 + 33), (100, 64 * 3), (150, 64 * 7 + 1), (512, 321)])
+def test_equal_pairs_over_several_tiles(gpu_ctx, m, n):
+    w = pairgen.Workload("equal", 0, (m,), 1, 0.3, fixed_E=0, seed=pairgen.SEED_BASE + 67)
+    _repeated(gpu_ctx, pairgen.generate(w, 0, 1999), n)
+
+
+@pytest.mark.parametrize("E", [1, 3, 4])
+def test_pairs_without_an_obstacle(gpu_ctx, E):
+    # Lists of more tiles than counts are loaded at a time, half of the pairs equal.
+    w = pairgen.Workload("free", 0, (100,), 1, 0.2, fixed_E=E, seed=pairgen.SEED_BASE + 71)
+    _repeated(gpu_ctx, pairgen.generate(w, 0, 64 * 63 + 5), 64 * 2048 * 17 + 77)
