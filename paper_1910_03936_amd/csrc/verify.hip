@@ -56,8 +56,12 @@ constexpr int kRefill = 16;
 // Waves per SIMD that a launch aims at: one / two / three / four take 81 / 71 / 72 / 72 us
 // for 4M pairs at E = 10 and 20 / 18.6 / 15.6 / 14.9 us for 4M of 100 bp at E = 3,
 // and three / four 147 / 131 us for 4M of 100 bp at E = 5, all selected (138 with a
-// lane per pair in step); fewer where the LDS holds fewer.
-constexpr uint32_t kVerifyWaves = 4;
+// lane per pair in step); fewer where the LDS holds fewer.  Three until a wave has
+// seven tiles (722k pairs of 100 bp at E = 6 12.6 us, 14.2 with four) and above
+// max_E 8 (1.9M of 150 bp at E = 10 53 and 56).
+uint32_t verify_waves(uint32_t n_tiles, int emax, int num_cus) {
+    return n_tiles >= 7u * 16u * (uint32_t)num_cus && emax <= 8 ? 4u : 3u;
+}
 
 // Rows of F: diagonals -emax - 1 .. emax + 1.
 __host__ __device__ constexpr uint32_t reach_rows(uint32_t emax) { return 2 * emax + 3; }
@@ -361,7 +365,7 @@ hipError_t launch_verify(const FilterParams& p, int emax, const uint32_t* sel, u
     uint32_t K = 1;
     for (;;) {
         const uint64_t fit = 160 * 1024 / verify_lds_bytes(p.wmax, (uint32_t)emax, K);
-        const uint64_t want = (uint64_t)num_cus * std::min<uint64_t>(4 * kVerifyWaves, fit);
+        const uint64_t want = (uint64_t)num_cus * std::min<uint64_t>(4 * verify_waves(p.n_tiles, emax, num_cus), fit);
         const uint64_t most = want * (emax >= 20 && p.n_tiles <= want * 2 * kVerifyTiles ? 2 * kVerifyTiles : kVerifyTiles);
         const uint64_t turns = std::max<uint64_t>(1, (p.n_tiles + most - 1) / most);
         const uint32_t need = (uint32_t)((p.n_tiles + want * turns - 1) / (want * turns));
