@@ -102,7 +102,8 @@ constexpr uint64_t kWavesPerSimd = 2;
 
 // Up to this threshold the pairs that SneakySnake found free of obstacles are left
 // out, which are then a large part of the accepted ones (10M related pairs of 250
-// bp at E = 1, half of them equal: 1777 -> 1129 us).
+// bp at E = 1, half of them equal: 1777 -> 1129 us), where a wave owns several tiles
+// (the counts of one are a trip to memory more: 0.5 us of 10).
 constexpr int kSkipFree = 3;
 
 // Intervals a lane holds (related pairs have about 2 E; 112 was the most seen
@@ -244,7 +245,7 @@ __global__ void __launch_bounds__(64) magnet_kernel(FilterParams P, uint32_t K) 
     for (uint32_t g = 0; g < n_here; g += 64) {
         const uint32_t i = g + (uint32_t)lane;
         bool take = chunk_bit(bits, g >> 6, lane) && i < n_here;
-        if constexpr (EMAX <= kSkipFree) {
+        if (EMAX <= kSkipFree && K > 1) {
             // A pair that SneakySnake crossed without an obstacle is one run.
             const uint32_t t = (g >> 6) % AHEAD;
             if (t == 0u) {
